@@ -58,7 +58,7 @@ def profiled_traffic():
     summary, or None once the attention source differs from the profiled one."""
     import hashlib
     src = b"".join(open(os.path.join(ROOT, "paper_2609_07008_amd", "csrc", f), "rb").read()
-                   for f in ("attend.hip", "common.h"))
+                   for f in ("attend_pair.hip", "attend.h", "common.h"))
     sha = hashlib.sha256(src).hexdigest()[:16]
     path = os.path.join(ROOT, "profiles", "mla_online_step_256k.md")
     if not os.path.exists(path):
@@ -693,7 +693,7 @@ def main():
         "hbm_gbs": {"oproj_add": round(oproj_bytes / t_opj / 1e9, 1)},
         "roofline": {"bound": "mfma", "achieved": round(att_tflops, 3), "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(att_tflops / PEAK_BF16_TFLOPS, 4), "traffic": profiled_traffic(),
-                     "kernel": "attend_kernel<512,64> (timed with the device plan kernels of "
+                     "kernel": "attend_pair_kernel<512,64> (timed with the device plan kernels of "
                                "mla_online_attend_planned)"},
     }
     out["clock"] = clock.report()
