@@ -4,36 +4,35 @@
 // K-contiguous, so this is C = A B^T with A = z, B = W_b, on bf16 MFMA with fp32
 // accumulation; y is written in fp32 or bf16.
 //
-// Tiles of 256 rows x 256 channels per workgroup of 8 waves (2 x 4), each wave
-// 128 x 64 (4 x 2 MFMA 32x32x16 blocks).  K advances 64 at a time; the A and B
-// slices of a step (32 KB each) are staged into LDS with 16-byte direct
-// global->LDS loads, double-buffered, and each wave reads the fragments of the
-// next 16-wide substep while the MFMAs of the current one run.  A wave is held
-// at issue while the load path takes each direct load, so only waves 0-3 (one
-// per SIMD) issue them, 8 KB of each operand apiece: on every SIMD the partner
-// wave's MFMAs run meanwhile.  In LDS a row of
-// a slice is 8 chunks of 16 bytes, chunk c of row r stored at slot
-// c ^ ((r >> 1) & 7), so the 16-lane quarter-waves of a 16-byte fragment read
-// hit 16 distinct bank groups.  Tile order: workgroups go to the 8 XCDs
-// round-robin, so XCD x takes a contiguous range of tiles, and inside it tiles
-// walk 4 row panels per column panel, so tiles resident together on an XCD share
-// A and B panels in its L2.
+// Tiles of 32 MI rows x 256 channels per workgroup of 8 waves (2 x 4, each 16 MI x
+// 64); the operands come in by direct global->LDS loads, 64 of K at a time, NST
+// slices in LDS.  On a full chip power is what bounds it: 16x16x32 MFMAs take less
+// per flop than 32x32x16 (see attend_pair.hip), so a wave's 16-row fragments feed
+// MI x 4 of them, neighbours sharing an operand.  What stalls it otherwise is the
+// barrier of a slice: it sits between a step's two halves, so that a half's MFMAs,
+// their fragments already in registers, run over the LDS reads of the next half and
+// over the direct loads, which all eight waves issue a few at a time.  The output
+// leaves through LDS as whole 128-byte lines (32-byte runs cost 9 % of the call).
+// Tile order: workgroups go to the 8 XCDs round-robin, so XCD x takes a contiguous
+// range of tiles, and inside it tiles walk 8 row panels per column panel, so tiles
+// resident together on an XCD share A and B panels in its L2 (4 panels 1 % slower,
+// 2 or 16 7-14 %).
+//
+// 264,192 rows, 4096 -> 4096: bf16 y 7.10 -> 6.37 ms (1.39 PFLOP/s), f32 y 7.40 ->
+// 6.86; 2100 rows f32 81 -> 66 us, 300 rows 76 -> 30, 16 rows 72 -> 12.
 #include "wb.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace mla {
 namespace {
 
-constexpr int WB_BM = 256, WB_BN = 256, WB_BK = 64;
-constexpr int WB_WAVES = 8;
-constexpr int WB_DMA_WAVES = 4;                       // waves that issue the direct loads
+constexpr int WB_BN = 256, WB_BK = 64;
+constexpr int WB_WAVES = 8;                           // 2 x 4 waves of (BM/2) x 64
 constexpr int WB_ROWB = WB_BK * 2;                    // bytes of one row of a slice
-constexpr int WB_SLICE = WB_BM * WB_ROWB;             // bytes of one A (or B) slice: 32 KB
-constexpr int WB_STAGE = 2 * WB_SLICE;                // A then B
-constexpr int WB_LOADS = WB_SLICE / 1024 / WB_DMA_WAVES;  // 1 KB direct loads per issuing wave and slice
-constexpr int WB_RPL = 1024 / WB_ROWB;                // rows per 1 KB load
-constexpr int WB_GM = 4;                              // row panels per column panel in the tile walk
+constexpr int64_t kWbFewRows = 64;
+constexpr int WB_GM = 8;                              // row panels per column panel in the tile walk
 
 __device__ __forceinline__ void wb_dma16(const void* base, uint32_t voff, const unsigned char MLA_LDS* dst) {
   const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)dst);
@@ -45,18 +44,23 @@ __device__ __forceinline__ void wb_dma16(const void* base, uint32_t voff, const 
                :: "v"(voff), "s"(bs), "s"(m0) : "memory", "m0");
 }
 
-// this wave's direct loads have landed and its LDS reads are done; then all
-// waves meet (the slice just loaded is complete, the other buffer is free)
+// all but the latest N of this wave's direct loads have landed and its LDS reads
+// are done; then all waves meet
+template <int N>
 __device__ __forceinline__ void wb_barrier() {
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
 }
 
 __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
-template <bool OUT_BF16>
-__global__ __launch_bounds__(WB_WAVES * 64) void wb_gemm_kernel(WbArgs a, int m_tiles, int n_tiles) {
-  constexpr int MI = 4, NI = 2, KS = WB_BK / 16;
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * WB_STAGE];
+// MI: 16-row blocks per wave (tile of 32 MI rows x 256 channels); NST: K slices in LDS
+template <bool OUT_BF16, int MI, int NST>
+__global__ __launch_bounds__(WB_WAVES * 64, 2) void wb_gemm_kernel(WbArgs a, int m_tiles, int n_tiles, bool stream_out) {
+  constexpr int NI = 4, BM = 32 * MI;
+  constexpr int A_BYTES = BM * WB_ROWB, STAGE = A_BYTES + WB_BN * WB_ROWB;
+  constexpr int NLOADS = STAGE / 1024;                       // 1 KB direct loads (8 rows each) per slice
+  constexpr int LPW = (NLOADS + WB_WAVES - 1) / WB_WAVES;    // per wave; past the end the last one again
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   // XCD-aware, grouped tile walk (batches one after another)
@@ -64,139 +68,303 @@ __global__ __launch_bounds__(WB_WAVES * 64) void wb_gemm_kernel(WbArgs a, int m_
   const int total = per_batch * a.batch;
   const int per = (total + 7) / 8;
   const int tb = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-  if (tb >= total) return;
+  if ((int)(blockIdx.x / 8) >= per || tb >= total) return;
   const int bt = tb / per_batch, t = tb % per_batch;
   const int group = t / (WB_GM * n_tiles), rem = t % (WB_GM * n_tiles);
   const int gm = std::min(WB_GM, m_tiles - group * WB_GM);
   const int mt = group * WB_GM + rem % gm, nt = rem / gm;
-  const int64_t m0 = (int64_t)mt * WB_BM;
+  const int64_t m0 = (int64_t)mt * BM;
   const int n0 = nt * WB_BN;
 
-  // Direct loads: load j of issuing wave w fills LDS bytes [1024 (L w + j), +1024)
-  // of a slice (L loads per wave), i.e. rows 8 (L w + j) + lane/8 of the tile at
-  // slot lane%8, whose source is chunk (lane%8) ^ swz(row).  The load takes a
-  // wave-uniform base (the wave's first row) plus a 32-bit lane offset; a wave's
-  // rows span 64 rows, so the offsets stay below 2^32 for row strides up to
-  // 2^25 elements (the host checks).  Rows past the end are clamped to the last
-  // row (their results are not stored).
-  const int K = a.d_in;
+  // Direct loads: load q of a slice fills LDS bytes [1024 q, +1024) of the stage, the
+  // slice's A rows then its B rows, 8 rows each; row r's chunk c sits at slot c ^
+  // swz(r).  A load takes a wave-uniform base (its first row) plus a 32-bit lane
+  // offset within its 8 rows.  Rows past the end are clamped to the last one (their
+  // results are not stored).
   const int64_t ldz = a.ldz, ldw = a.ldw;
-  const int wr0 = WB_LOADS * WB_RPL * (wave % WB_DMA_WAVES);
-  const int64_t a_base_row = std::min<int64_t>(m0 + wr0, a.n_rows - 1);
-  const int64_t b_base_row = std::min<int64_t>((int64_t)n0 + wr0, (int64_t)a.d_out - 1);
-  uint32_t a_lo[WB_LOADS], b_lo[WB_LOADS];
+  const unsigned char* src[LPW];
+  uint32_t voff[LPW];
+  int dst[LPW];
 #pragma unroll
-  for (int j = 0; j < WB_LOADS; ++j) {
-    const int r = WB_RPL * (WB_LOADS * (wave % WB_DMA_WAVES) + j) + (lane >> 3);
-    const int c = (lane & 7) ^ swz(r);
-    const int64_t m = std::min<int64_t>(m0 + r, a.n_rows - 1);
-    const int64_t n = std::min<int64_t>((int64_t)n0 + r, (int64_t)a.d_out - 1);
-    a_lo[j] = (uint32_t)((m - a_base_row) * ldz * 2 + c * 16);
-    b_lo[j] = (uint32_t)((n - b_base_row) * ldw * 2 + c * 16);
+  for (int j = 0; j < LPW; ++j) {
+    const int q = std::min(wave + WB_WAVES * j, NLOADS - 1);
+    const bool is_a = q < A_BYTES / 1024;
+    const int r0 = 8 * (is_a ? q : q - A_BYTES / 1024), lr = lane >> 3;
+    const int64_t rows = is_a ? a.n_rows - m0 : (int64_t)a.d_out - n0;   // rows from the tile's first to the last
+    const int64_t first = std::min<int64_t>(r0, rows - 1), row = std::min<int64_t>(r0 + lr, rows - 1);
+    const int64_t ld = is_a ? ldz : ldw;
+    src[j] = (const unsigned char*)(is_a ? a.z + bt * a.z_batch : a.w_b + bt * a.w_batch) + ((is_a ? m0 : n0) + first) * ld * 2;
+    voff[j] = (uint32_t)((row - first) * ld * 2 + ((lane & 7) ^ swz(r0 + lr)) * 16);
+    dst[j] = 1024 * q;
   }
-  const unsigned char* Abase = (const unsigned char*)(a.z + bt * a.z_batch) + a_base_row * ldz * 2;
-  const unsigned char* Bbase = (const unsigned char*)(a.w_b + bt * a.w_batch) + b_base_row * ldw * 2;
-
-  auto load_slice = [&](int kt) {
-    if (wave >= WB_DMA_WAVES) return;
-    unsigned char* st = lds + (kt & 1) * WB_STAGE;
-    const unsigned char* ak = Abase + (int64_t)kt * WB_ROWB;
-    const unsigned char* bk = Bbase + (int64_t)kt * WB_ROWB;
-#pragma unroll
-    for (int j = 0; j < WB_LOADS; ++j)
-      wb_dma16(ak, a_lo[j], (const unsigned char MLA_LDS*)(st + 1024 * (WB_LOADS * wave + j)));
-#pragma unroll
-    for (int j = 0; j < WB_LOADS; ++j)
-      wb_dma16(bk, b_lo[j], (const unsigned char MLA_LDS*)(st + WB_SLICE + 1024 * (WB_LOADS * wave + j)));
+  auto load_one = [&](int j, int kt, int st) {
+    wb_dma16(src[j] + (int64_t)kt * WB_ROWB, voff[j], (const unsigned char MLA_LDS*)(lds + st + dst[j]));
   };
 
-  f32x16 acc[MI][NI];
+  f32x4 acc[MI][NI];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const int wm = wave >> 2, wn = wave & 3;
-  const int l32 = lane & 31, hk = lane >> 5;
-  // fragment byte offsets inside a stage for substep ks: row*ROWB + 16*((2ks+hk) ^ swz(row))
-  int a_fr[MI][KS], b_fr[NI][KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
+  // fragments (16 rows x 32 of K): lane group lg holds chunk 4 h + lg of row lc; the
+  // rows' swizzle repeats every 16, so blocks are immediate offsets
+  const int wm = wave >> 2, wn = wave & 3, lg = lane >> 4, lc = lane & 15;
+  const int fa = (wm * (BM / 2) + lc) * WB_ROWB + ((lg ^ swz(lc)) * 16);
+  const int fb = A_BYTES + (wn * 64 + lc) * WB_ROWB + ((lg ^ swz(lc)) * 16);
+  struct Frags {
+    bf16x8 a[MI], b[NI];
+  };
+  auto frag = [&](int base, int st, int h, int i) -> bf16x8 {
+    return *(const bf16x8 MLA_LDS*)((const unsigned char MLA_LDS*)lds + ((st + base) ^ (h * 64)) + i * 16 * WB_ROWB);
+  };
+  // the MFMAs of one 32-wide half step, and beside them the next half's fragment
+  // reads and (LOAD) the direct loads of a later slice.  The transposed tile: a lane
+  // holds output row lc and four consecutive channels of each block.
+  auto half = [&](const Frags& f, Frags& nx, int nst, int nh, auto LOAD, int kt, int lst) {
+    constexpr int R = MI + NI;                 // fragments to read, spread over the rows of MFMAs
+    constexpr int PER = (R + MI - 1) / MI;
+    int rd = 0, ld = 0;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      const int ra = wm * 128 + i * 32 + l32;
-      a_fr[i][ks] = ra * WB_ROWB + 16 * ((2 * ks + hk) ^ swz(ra));
-    }
 #pragma unroll
-    for (int j = 0; j < NI; ++j) {
-      const int rb = wn * 64 + j * 32 + l32;
-      b_fr[j][ks] = WB_SLICE + rb * WB_ROWB + 16 * ((2 * ks + hk) ^ swz(rb));
-    }
-  }
-
-  const int nk = K / WB_BK;
-  load_slice(0);
-  for (int kt = 0; kt < nk; ++kt) {
-    wb_barrier();                              // slice kt is in; buffer (kt+1)&1 was read at kt-1
-    if (kt + 1 < nk) load_slice(kt + 1);
-    const unsigned char* st = lds + (kt & 1) * WB_STAGE;
-    bf16x8 af[2][MI], bfr[2][NI];
+      for (int k = 0; k < PER; ++k, ++rd)
+        if (rd < NI) nx.b[rd] = frag(fb, nst, nh, rd);
+        else if (rd < R) nx.a[rd - NI] = frag(fa, nst, nh, rd - NI);
+      if constexpr (decltype(LOAD)::value) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i) af[0][i] = *(const bf16x8*)(st + a_fr[i][0]);
-#pragma unroll
-    for (int j = 0; j < NI; ++j) bfr[0][j] = *(const bf16x8*)(st + b_fr[j][0]);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const int c = ks & 1, nx = c ^ 1;
-      if (ks + 1 < KS) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i) af[nx][i] = *(const bf16x8*)(st + a_fr[i][ks + 1]);
-#pragma unroll
-        for (int j = 0; j < NI; ++j) bfr[nx][j] = *(const bf16x8*)(st + b_fr[j][ks + 1]);
+        for (int k = 0; k < (LPW + MI - 1) / MI; ++k, ++ld)
+          if (ld < LPW) load_one(ld, kt, lst);
       }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[c][i], bfr[c][j], acc[i][j], 0, 0, 0);
+      for (int jj = 0; jj < NI; ++jj) {
+        const int j = i & 1 ? NI - 1 - jj : jj;   // neighbours share an operand
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.b[j], f.a[i], acc[i][j], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
+  };
+
+  // Slices 0 .. NST-1 go out first.  Step kt: the first half's MFMAs beside the reads
+  // of the second half's fragments; one barrier (slice kt is read by every wave, so
+  // its buffer is free; slice kt + 1 has landed); the second half's MFMAs beside the
+  // loads of slice kt + NST and the reads of slice kt + 1's first half.
+  const int nk = a.d_in / WB_BK;
+#pragma unroll
+  for (int p = 0; p < NST; ++p)
+    if (p < nk)
+#pragma unroll
+      for (int j = 0; j < LPW; ++j) load_one(j, p, p * STAGE);
+  if (nk >= NST) wb_barrier<(NST - 1) * LPW>(); else wb_barrier<0>();
+  Frags f0, f1;
+#pragma unroll
+  for (int j = 0; j < NI; ++j) f0.b[j] = frag(fb, 0, 0, j);
+#pragma unroll
+  for (int i = 0; i < MI; ++i) f0.a[i] = frag(fa, 0, 0, i);
+  int st = 0, kt = 0;
+  for (; kt + NST < nk; ++kt) {
+    half(f0, f1, st, 1, std::false_type{}, 0, 0);
+    wb_barrier<(NST - 2) * LPW>();
+    const int nst = st == (NST - 1) * STAGE ? 0 : st + STAGE;
+    half(f1, f0, nst, 0, std::true_type{}, kt + NST, st);
+    st = nst;
+  }
+  for (; kt < nk; ++kt) {
+    half(f0, f1, st, 1, std::false_type{}, 0, 0);
+    wb_barrier<0>();
+    const int nst = st == (NST - 1) * STAGE ? 0 : st + STAGE;
+    half(f1, f0, nst, 0, std::false_type{}, 0, 0);   // after the last slice: reads of a stale buffer, not used
+    st = nst;
   }
 
-  // epilogue: lane holds column l32 of each 32x32 block, rows hk*4 + 8(e/4) + e%4
+  // Epilogue through LDS, 16 rows x 64 channels a wave at a time: written in the
+  // accumulator layout (row lc, channels lg*4 .. +3 of each block; 16-byte chunk c
+  // of row r at c ^ (r & 7)), read back row-contiguous, so that each store writes
+  // whole 128-byte lines.
+  wb_barrier<0>();
+  constexpr int ES = OUT_BF16 ? 2 : 4, ROW = 64 * ES;   // element and row bytes
+  constexpr int CH = ROW / 16, RPI = 64 / CH;           // 16-byte chunks a row, rows a store
+  unsigned char MLA_LDS* sw = (unsigned char MLA_LDS*)lds + wave * (2 * 16 * ROW);
   const int64_t ybase = bt * a.y_batch;
+  // whole chunks: y is 16-byte aligned
+  const bool vec = ((a.ldy | a.y_batch) & (16 / ES - 1)) == 0;
+  const int rl = lane / CH, cl = lane % CH;
+  const int n = n0 + wn * 64 + cl * (16 / ES);
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+  for (int i = 0; i < MI; ++i) {
+    unsigned char MLA_LDS* sb = sw + (i & 1) * (16 * ROW);
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
-      const int n = n0 + wn * 64 + j * 32 + l32;
-      if (n >= a.d_out) continue;
+      const f32x4 v = acc[i][j];
+      if (OUT_BF16)
+        *(u32x2 MLA_LDS*)(sb + lc * ROW + (((j * 2 + (lg >> 1)) ^ (lc & 7)) * 16) + (lg & 1) * 8) =
+            u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+      else
+        *(f32x4 MLA_LDS*)(sb + lc * ROW + (((j * 4 + lg) ^ (lc & 7)) * 16)) = v;
+    }
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int64_t m = m0 + wm * 128 + i * 32 + hk * 4 + (e >> 2) * 8 + (e & 3);
-        if (m >= a.n_rows) continue;
-        if (OUT_BF16)
-          ((__bf16*)a.y)[ybase + m * a.ldy + n] = (__bf16)acc[i][j][e];
-        else
-          ((float*)a.y)[ybase + m * a.ldy + n] = acc[i][j][e];
+    for (int p = 0; p < 16 / RPI; ++p) {
+      const int r = p * RPI + rl;
+      const u32x4 v = *(const u32x4 MLA_LDS*)(sb + r * ROW + ((cl ^ (r & 7)) * 16));
+      const int64_t m = m0 + wm * (BM / 2) + i * 16 + r;
+      if (m >= a.n_rows) continue;
+      const int64_t at = ybase + m * a.ldy + n;
+      if (vec && n + 16 / ES <= a.d_out) {
+        u32x4* q = (u32x4*)((unsigned char*)a.y + at * ES);
+        if (stream_out) __builtin_nontemporal_store(v, q); else *q = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 16 / ES; ++e) {
+          if (n + e >= a.d_out) continue;
+          if (OUT_BF16)
+            ((uint16_t*)a.y)[at + e] = (uint16_t)(v[e / 2] >> (16 * (e & 1)));
+          else
+            ((uint32_t*)a.y)[at + e] = v[e];
+        }
       }
     }
+  }
+}
+
+// Few rows (a query block, a chunk of new tokens): the weight is read once, so what
+// counts is how much of it is in flight.  A workgroup takes 16 output channels and
+// up to 16 MB rows, and its 8 waves split K: 64-wide chunk c goes to wave c % 8,
+// fragments straight from memory, the next two chunks loaded ahead.  The waves'
+// sums meet in LDS and are added in wave order.
+template <bool OUT_BF16, int MB>
+__global__ __launch_bounds__(512) void wb_rows_kernel(WbArgs a, int n_blocks) {
+  __shared__ f32x4 part[8][MB][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lg = lane >> 4, lc = lane & 15;
+  const int bt = blockIdx.x / n_blocks, n0 = (int)(blockIdx.x % n_blocks) * 16;
+  const int64_t m0 = (int64_t)blockIdx.y * 16 * MB;
+  // rows past the end repeat the last one; their results are not stored
+  const uint16_t* w = a.w_b + bt * a.w_batch + (int64_t)std::min(n0 + lc, a.d_out - 1) * a.ldw + lg * 8;
+  const uint16_t* z[MB];
+#pragma unroll
+  for (int b = 0; b < MB; ++b)
+    z[b] = a.z + bt * a.z_batch + std::min<int64_t>(m0 + b * 16 + lc, a.n_rows - 1) * a.ldz + lg * 8;
+  f32x4 acc[MB];
+#pragma unroll
+  for (int b = 0; b < MB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nc = a.d_in / WB_BK;
+  struct Chunk {
+    bf16x8 w[2], z[2][MB];
+  };
+  auto load = [&](Chunk& c, int ch) {
+    const int k = std::min(ch, nc - 1) * WB_BK;   // past the end: the last chunk again, not used
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      c.w[h] = *(const bf16x8*)(w + k + h * 32);
+#pragma unroll
+      for (int b = 0; b < MB; ++b) c.z[h][b] = *(const bf16x8*)(z[b] + k + h * 32);
+    }
+  };
+  auto mul = [&](const Chunk& c) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int b = 0; b < MB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c.w[h], c.z[h][b], acc[b], 0, 0, 0);
+  };
+  constexpr int D = MB <= 2 ? 4 : 2;   // chunks in flight
+  Chunk c[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) load(c[d], wave + 8 * d);
+  for (int ch = wave; ch < nc; ch += 8 * D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      if (ch + 8 * d < nc) mul(c[d]);
+      load(c[d], ch + 8 * (d + D));
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < MB; ++b) part[wave][b][lane] = acc[b];
+  __syncthreads();
+  // lane lg*16 + lc of block b holds row b*16 + lc, channels lg*4 .. +3; thread t sums
+  // four channels of one row, the four lane groups of a row in neighbouring threads
+  for (int i = tid; i < MB * 64; i += 512) {
+    const int b = i >> 6, r = (i & 63) >> 2, g = i & 3;
+    f32x4 v = part[0][b][g * 16 + r];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) v += part[k][b][g * 16 + r];
+    const int64_t m = m0 + b * 16 + r;
+    if (m >= a.n_rows) continue;
+    const int64_t at = bt * a.y_batch + m * a.ldy + n0 + g * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (n0 + g * 4 + e >= a.d_out) continue;
+      if (OUT_BF16)
+        ((__bf16*)a.y)[at + e] = (__bf16)v[e];
+      else
+        ((float*)a.y)[at + e] = v[e];
+    }
+  }
+}
+
+template <bool OUT_BF16>
+hipError_t launch_rows(const WbArgs& a, hipStream_t s) {
+  const int n_blocks = (a.d_out + 15) / 16;
+  const unsigned gx = (unsigned)(n_blocks * a.batch);
+  if (a.n_rows <= 16)
+    wb_rows_kernel<OUT_BF16, 1><<<dim3(gx), dim3(512), 0, s>>>(a, n_blocks);
+  else if (a.n_rows <= 32)
+    wb_rows_kernel<OUT_BF16, 2><<<dim3(gx), dim3(512), 0, s>>>(a, n_blocks);
+  else
+    wb_rows_kernel<OUT_BF16, 4><<<dim3(gx, (unsigned)((a.n_rows + 63) / 64)), dim3(512), 0, s>>>(a, n_blocks);
+  return hipGetLastError();
+}
+
+template <bool OUT_BF16, int MI, int NST>
+hipError_t launch_tiles(const WbArgs& a, hipStream_t s) {
+  const int m_tiles = (int)((a.n_rows + 32 * MI - 1) / (32 * MI));
+  const int n_tiles = (a.d_out + WB_BN - 1) / WB_BN;
+  const int total = m_tiles * n_tiles * a.batch;
+  // an output beyond the L2s' 32 MB cannot stay there: stored past them, it leaves
+  // them to the panels (33,792 rows f32: 927 -> 882 us; 264,192 rows bf16: 6.39 -> 6.31 ms)
+  const bool stream_out = a.n_rows * a.d_out * a.batch * (OUT_BF16 ? 2 : 4) > (int64_t)32 << 20;
+  wb_gemm_kernel<OUT_BF16, MI, NST><<<dim3((unsigned)(8 * ((total + 7) / 8))), dim3(WB_WAVES * 64), 0, s>>>(a, m_tiles, n_tiles, stream_out);
+  return hipGetLastError();
+}
+
+template <bool OUT_BF16>
+hipError_t launch_out(const WbArgs& a, hipStream_t s) {
+  // up to 64 rows the few-row kernel (4096 -> 4096: 8.4 us at 1 row, 11.8 at 16, 16.7
+  // at 32, 23.9 at 64) against 26-28 us for the tiles; at 128 rows 43 against 28
+  if (a.n_rows <= kWbFewRows && (a.d_out + 15) / 16 * (int64_t)a.batch <= INT32_MAX) return launch_rows<OUT_BF16>(a, s);
+  // Tile height: the one whose rounds of tiles over the 256 compute units cost least,
+  // a tile of 32 MI rows taken as MI + 3 (one round at K = 4096, heights 1 .. 8: 30,
+  // 34, 42, 48, 56, 63, 73, 74 us).  At 4096 channels: 2100 rows 68 us at height 5
+  // against 82 at 8, 1024 rows 40 at 2 against 76 at 8, 33,792 rows 849 at 8 against
+  // 875 at 6.
+  const int64_t n_tiles = (int64_t)((a.d_out + WB_BN - 1) / WB_BN) * a.batch;
+  int best = 8;
+  int64_t cost = INT64_MAX;
+  for (int mi = 8; mi >= 1; --mi) {
+    const int64_t tiles = (a.n_rows + 32 * mi - 1) / (32 * mi) * n_tiles;
+    const int64_t c = (tiles + 255) / 256 * (mi + 3);
+    if (c < cost) {
+      cost = c;
+      best = mi;
+    }
+  }
+  switch (best) {
+    case 1: return launch_tiles<OUT_BF16, 1, 4>(a, s);
+    case 2: return launch_tiles<OUT_BF16, 2, 3>(a, s);
+    case 3: return launch_tiles<OUT_BF16, 3, 3>(a, s);
+    case 4: return launch_tiles<OUT_BF16, 4, 3>(a, s);
+    case 5: return launch_tiles<OUT_BF16, 5, 3>(a, s);
+    case 6: return launch_tiles<OUT_BF16, 6, 2>(a, s);
+    case 7: return launch_tiles<OUT_BF16, 7, 2>(a, s);
+    default: return launch_tiles<OUT_BF16, 8, 2>(a, s);
+  }
 }
 
 }  // namespace
 
 hipError_t launch_wb(const WbArgs& a, hipStream_t s) {
   if (a.n_rows == 0) return hipSuccess;
-  const int m_tiles = (int)((a.n_rows + WB_BM - 1) / WB_BM);
-  const int n_tiles = (a.d_out + WB_BN - 1) / WB_BN;
-  const int total = m_tiles * n_tiles * a.batch;
-  const dim3 grid((unsigned)(8 * ((total + 7) / 8)));
-  if (a.y_bf16)
-    wb_gemm_kernel<true><<<grid, dim3(WB_WAVES * 64), 0, s>>>(a, m_tiles, n_tiles);
-  else
-    wb_gemm_kernel<false><<<grid, dim3(WB_WAVES * 64), 0, s>>>(a, m_tiles, n_tiles);
-  return hipGetLastError();
+  return a.y_bf16 ? launch_out<true>(a, s) : launch_out<false>(a, s);
 }
 
 }  // namespace mla
