@@ -868,8 +868,6 @@ mla_status attend_planned_impl(const mla_geom* geom, const mla_plan_info* info, 
   d.group_base = reinterpret_cast<int32_t*>(W + L[W_GROUP_BASE]);
   d.items = reinterpret_cast<mla::WorkItem*>(W + L[W_ITEMS]);
   d.status_out = status;
-  hipError_t e = mla::launch_dplan(d, s);
-  if (e != hipSuccess) return hip_fail(e, "plan kernels");
 
   mla::AttendArgs a{};
   a.kv = kv;
@@ -912,7 +910,8 @@ mla_status attend_planned_impl(const mla_geom* geom, const mla_plan_info* info, 
     a.part_lse = reinterpret_cast<float*>(W + L[W_PART_LSE]);
   }
   a.rot = L[W_ROT] >= 0 ? reinterpret_cast<float*>(W + L[W_ROT]) : nullptr;
-  if ((e = mla::launch_plan(a, s)) != hipSuccess) return hip_fail(e, "plan kernels");
+  hipError_t e = mla::launch_dplan(d, a, s);
+  if (e != hipSuccess) return hip_fail(e, "plan kernels");
   if ((e = mla::launch_attend(a, s)) != hipSuccess) return hip_fail(e, "attention kernel");
   if (!info->one_chunk) {
     e = mla::launch_merge(info->max_slots, a.dv, a.part_o, a.part_lse, a.part_ptr, out_dtype, out_o, out_lse, s,

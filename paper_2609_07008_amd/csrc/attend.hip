@@ -1,6 +1,6 @@
 // Query-side RoPE relocation and segment-wise absorbed-MLA attention over the
-// packed latent stream (Sec. 2.3 eq:rope, Alg. 2 SelectiveMLA), plus the
-// device half of the plan (partial index, segment bookkeeping, protected flags).
+// packed latent stream (Sec. 2.3 eq:rope, Alg. 2 SelectiveMLA): the rotary value and
+// the 64 + 16 latent (attend_pair.hip: the 512 + 64 latent as the value).
 //
 // Work item = up to 128 head-rows (query rows x heads) that share every key of
 // the single latent stream (the latent is never split per head, Sec. 2.1).
@@ -633,92 +633,6 @@ __global__ __launch_bounds__(256, 1) void attend_kernel(AttendArgs a) {
     }
   if (ROT) rot_store(dst + DC, half, vr);
   if (half == 0) a.part_lse[pidx] = (m_run + __log2f(l_tot)) * 0.6931471805599453f;
-}
-
-
-// ----------------------------------------------------------------------------
-// device half of the plan
-// ----------------------------------------------------------------------------
-// segment (storage order) holding storage row r: the last one whose kv_start <= r
-__device__ __forceinline__ int segment_of_row(const AttendArgs& a, int64_t r) {
-  int lo = 0, hi = a.n_segs - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (a.segs[a.storage[mid]].kv_start <= r) lo = mid; else hi = mid - 1;
-  }
-  return a.storage[lo];
-}
-
-__global__ __launch_bounds__(256) void plan_slots_kernel(AttendArgs a) {
-  const SegInfo* segs = a.segs;
-  const int64_t n_slots = a.dyn != nullptr ? a.dyn->n_slots : a.n_slots;
-  const int64_t n_parts = a.dyn != nullptr ? a.dyn->n_parts : a.n_parts;
-  const int64_t nglob = a.n_rows * a.n_groups;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= n_slots;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    if (i == n_slots) {
-      a.part_ptr[i] = n_parts;
-      continue;
-    }
-    int s;
-    int64_t base;
-    if (i < nglob) {
-      const int64_t r = i / a.n_groups, g = i - r * a.n_groups;
-      s = segment_of_row(a, r);
-      const SegInfo si = segs[s];
-      base = si.cum_global + ((r - si.kv_start) * a.n_groups + g) * si.n_chunks;
-    } else {
-      const int64_t k = i - nglob;
-      const int64_t ai = k / a.n_local, jj = k - ai * a.n_local;
-      if (a.dyn == nullptr) {
-        s = a.prot_seg[ai];
-        base = a.global_parts + a.cum_local[ai] + jj * segs[s].n_chunks;
-      } else {
-        s = segment_of_row(a, a.prot[ai]);
-        const int64_t nch = segs[s].n_chunks;
-        base = a.global_parts + a.seg_local_base[s] + ((ai - a.seg_prot_lo[s]) * a.n_local + jj) * nch;
-      }
-    }
-    a.part_ptr[i] = base;
-    if (a.part_seg != nullptr) {
-      const SegInfo si = segs[s];
-      for (int c = 0; c < si.n_chunks; ++c) {
-        const ChunkInfo ch = a.chunks[si.chunk_off + c];
-        a.part_seg[2 * (base + c)] = a.rank_seg[ch.first_rank];
-        a.part_seg[2 * (base + c) + 1] = a.rank_seg[ch.last_rank];
-      }
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void row_src_kernel(AttendArgs a) {
-  const int32_t* prot = a.prot;
-  const int n_prot = a.dyn != nullptr ? a.dyn->n_prot : a.n_prot;
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < a.n_rows;
-       r += (int64_t)gridDim.x * blockDim.x) {
-    int lo = 0, hi = n_prot;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (prot[mid] < r) lo = mid + 1; else hi = mid;
-    }
-    a.row_src[r] = (lo < n_prot && prot[lo] == r) ? 1 : 0;
-  }
-}
-
-// part_ptr / part_seg (when part_ptr is set) and row_src (when set); grids cover
-// the host count of slots and rows (for a device plan, the capacity bound)
-hipError_t launch_plan(const AttendArgs& a, hipStream_t s) {
-  if (a.part_ptr != nullptr) {
-    const int64_t n = a.n_slots + 1;
-    const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, 8192);
-    plan_slots_kernel<<<dim3(blocks), dim3(256), 0, s>>>(a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (a.row_src == nullptr) return hipSuccess;
-  const unsigned rb = (unsigned)std::min<int64_t>((a.n_rows + 255) / 256, 4096);
-  row_src_kernel<<<dim3(rb), dim3(256), 0, s>>>(a);
-  return hipGetLastError();
 }
 
 hipError_t launch_attend(const AttendArgs& a, hipStream_t s) {

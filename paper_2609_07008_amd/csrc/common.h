@@ -179,7 +179,8 @@ struct DPlanArgs {
   WorkItem* items;           // [max_items]
   int32_t* status_out;       // device int32 or NULL
 };
-hipError_t launch_dplan(const DPlanArgs& a, hipStream_t s);
+// with the partial index and the protected flags of the same call (a.dyn == d.dyn)
+hipError_t launch_dplan(const DPlanArgs& d, const AttendArgs& a, hipStream_t s);
 
 // ----------------------------------------------------------------------------
 // device helpers

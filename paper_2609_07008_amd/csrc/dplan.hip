@@ -1,29 +1,40 @@
-// Device half of a device-built plan (Alg. 2: ProtectedRows feeding
-// SelectiveMLA in the same layer without a trip through the host).
+// Device half of the plan (Alg. 2: ProtectedRows feeding SelectiveMLA in the same
+// layer without a trip through the host): the work items, the partial index with
+// its segment bookkeeping, and the protected flags.
 //
 // The host fixes, once per request, everything that depends only on the segment
 // table: segment visibility in request order, the chunking of each visible list,
 // the Global partial index and the launch order of the item groups (one group
 // per kind, segment and chunk, largest upper-bound cost first).  Per call, the
-// protected rows A and |A| are read from device memory and two kernels finish
-// the plan:
-//   dplan_count_kernel (one workgroup)  validates A (ascending, in range, at most
-//     the capacity the plan was built for), finds each segment's run of
-//     protected rows by binary search (A is sorted and segments are contiguous
-//     in storage), the Local partial base of each segment (a scan in storage
-//     order), each group's item count and their prefix (a scan in launch order),
-//     and the call's counts;
-//   dplan_items_kernel (one thread per item bound)  writes each work item: its
-//     group by binary search in the prefix, then its head-row range.  Inside a
-//     group items run from the segment's last head-rows down, so that the
-//     costliest items of the group start first.
+// protected rows A and |A| are read from device memory and the plan is finished:
+//   count  validates A (ascending, in range, at most the capacity the plan was
+//     built for), finds each segment's run of protected rows by binary search (A is
+//     sorted and segments are contiguous in storage), the Local partial base of
+//     each segment (a scan in storage order), each group's item count and their
+//     prefix (a scan in launch order), and the call's counts;
+//   items  one thread per item: its group by binary search in the prefix, then its
+//     head-row range.  Inside a group items run from the segment's last head-rows
+//     down, so that the costliest items of the group start first;
+//   slots  one thread per slot: part_ptr and part_seg;
+//   rows   one thread per row: row_src.
 // A rejected A leaves zero items, zero slots and status MLA_ERR_ROWS: the
 // attention kernels then do nothing.
+//
+// What bounds it is launches: every phase is a chain of a few dependent reads.
+// Requests of up to kPlanOneRows rows take one launch, in which every workgroup
+// counts for itself, in LDS, and takes its share of items, slots and rows (the
+// 2.1K-row step's four plan launches 21 us, this one 9.6); above that the count reads
+// too long a list to be repeated, and the phases are launches of their own.
 #include "common.h"
+
+#include <algorithm>
 
 namespace mla {
 
 constexpr int kPlanThreads = 1024;
+// protected lists up to this length are searched in LDS: the binary searches of the
+// segments' runs are chains of a dozen dependent reads
+constexpr int kPlanLdsRows = 8192;
 
 // exclusive prefix of v over the workgroup's threads (in thread order); *total
 // receives the sum.  Every thread of the workgroup calls it.
@@ -49,7 +60,8 @@ __device__ int64_t block_exclusive_scan(int64_t v, int64_t* total) {
 }
 
 // first index in prot[0, n) whose value is >= r
-__device__ __forceinline__ int lower_bound_i32(const int32_t* prot, int n, int64_t r) {
+template <class P>
+__device__ __forceinline__ int lower_bound_i32(P prot, int n, int64_t r) {
   int lo = 0, hi = n;
   while (lo < hi) {
     const int mid = (lo + hi) >> 1;
@@ -58,7 +70,9 @@ __device__ __forceinline__ int lower_bound_i32(const int32_t* prot, int n, int64
   return lo;
 }
 
-__global__ __launch_bounds__(kPlanThreads) void dplan_count_kernel(DPlanArgs a) {
+// the count phase, by one workgroup; a's tables are its outputs, in device memory
+// or in LDS (generic pointers)
+__device__ void plan_count(const DPlanArgs& a, int32_t MLA_LDS* s_prot) {   // [kPlanLdsRows]
   __shared__ int s_ok;
   __shared__ int s_np;
   const int tid = threadIdx.x;
@@ -71,8 +85,10 @@ __global__ __launch_bounds__(kPlanThreads) void dplan_count_kernel(DPlanArgs a) 
   const int np = s_ok ? s_np : 0;
   // validation: rows in range and strictly increasing
   int bad = 0;
+  const bool in_lds = np <= kPlanLdsRows;
   for (int i = tid; i < np; i += kPlanThreads) {
     const int32_t r = a.prot[i];
+    if (in_lds) s_prot[i] = r;
     if (r < 0 || (int64_t)r >= a.n_rows || (i > 0 && a.prot[i - 1] >= r)) bad = 1;
   }
   if (__syncthreads_or(bad) || !s_ok) {
@@ -94,8 +110,10 @@ __global__ __launch_bounds__(kPlanThreads) void dplan_count_kernel(DPlanArgs a) 
     if (i < a.n_segs) {
       const int s = a.storage[i];
       const SegInfo si = a.segs[s];
-      const int lo = lower_bound_i32(a.prot, np, si.kv_start);
-      const int hi = lower_bound_i32(a.prot, np, si.kv_start + si.length);
+      const int lo = in_lds ? lower_bound_i32(s_prot, np, si.kv_start)
+                            : lower_bound_i32(a.prot, np, si.kv_start);
+      const int hi = in_lds ? lower_bound_i32(s_prot, np, si.kv_start + si.length)
+                            : lower_bound_i32(a.prot, np, si.kv_start + si.length);
       a.seg_prot_lo[s] = lo;
       a.seg_prot_cnt[s] = hi - lo;
       parts = (int64_t)(hi - lo) * a.n_local * si.n_chunks;
@@ -136,9 +154,12 @@ __global__ __launch_bounds__(kPlanThreads) void dplan_count_kernel(DPlanArgs a) 
   }
 }
 
-__global__ __launch_bounds__(256) void dplan_items_kernel(DPlanArgs a) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= a.dyn->n_items) return;
+__global__ __launch_bounds__(kPlanThreads) void dplan_count_kernel(DPlanArgs a) {
+  __shared__ int32_t s_prot[kPlanLdsRows];
+  plan_count(a, (int32_t MLA_LDS*)s_prot);
+}
+
+__device__ void plan_item(const DPlanArgs& a, int i, WorkItem* items) {
   // the group holding item i: the last g with group_base[g] <= i
   int lo = 0, hi = a.n_item_groups - 1;
   while (lo < hi) {
@@ -167,15 +188,169 @@ __global__ __launch_bounds__(256) void dplan_items_kernel(DPlanArgs a) {
   w.chunk = g.chunk;
   w.max_u = (int32_t)(last_row - si.kv_start);
   w.pad = 0;
-  a.items[i] = w;
+  items[i] = w;
 }
 
-hipError_t launch_dplan(const DPlanArgs& a, hipStream_t s) {
-  dplan_count_kernel<<<dim3(1), dim3(kPlanThreads), 0, s>>>(a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.max_items == 0) return e;
-  dplan_items_kernel<<<dim3((unsigned)((a.max_items + 255) / 256)), dim3(256), 0, s>>>(a);
+__global__ __launch_bounds__(256) void dplan_items_kernel(DPlanArgs a) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < a.dyn->n_items) plan_item(a, i, a.items);
+}
+
+
+// segment (storage order) holding storage row r: the last one whose kv_start <= r
+__device__ __forceinline__ int segment_of_row(const AttendArgs& a, int64_t r) {
+  int lo = 0, hi = a.n_segs - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (a.segs[a.storage[mid]].kv_start <= r) lo = mid; else hi = mid - 1;
+  }
+  return a.storage[lo];
+}
+
+// part_ptr (and part_seg) of slot i; i = n_slots closes the index; seg_of(r): the
+// segment of storage row r
+template <class SegOf>
+__device__ __forceinline__ void plan_slot(const AttendArgs& a, int64_t i, int64_t n_slots, int64_t n_parts, SegOf seg_of) {
+  const int64_t nglob = a.n_rows * a.n_groups;
+  if (i == n_slots) {
+    a.part_ptr[i] = n_parts;
+    return;
+  }
+  int s;
+  int64_t base;
+  if (i < nglob) {
+    const int64_t r = i / a.n_groups, g = i - r * a.n_groups;
+    s = seg_of(r);
+    const SegInfo si = a.segs[s];
+    base = si.cum_global + ((r - si.kv_start) * a.n_groups + g) * si.n_chunks;
+  } else {
+    const int64_t k = i - nglob;
+    const int64_t ai = k / a.n_local, jj = k - ai * a.n_local;
+    if (a.dyn == nullptr) {
+      s = a.prot_seg[ai];
+      base = a.global_parts + a.cum_local[ai] + jj * a.segs[s].n_chunks;
+    } else {
+      s = seg_of((int64_t)a.prot[ai]);
+      const int64_t nch = a.segs[s].n_chunks;
+      base = a.global_parts + a.seg_local_base[s] + ((ai - a.seg_prot_lo[s]) * a.n_local + jj) * nch;
+    }
+  }
+  a.part_ptr[i] = base;
+  if (a.part_seg != nullptr) {
+    const SegInfo si = a.segs[s];
+    for (int c = 0; c < si.n_chunks; ++c) {
+      const ChunkInfo ch = a.chunks[si.chunk_off + c];
+      a.part_seg[2 * (base + c)] = a.rank_seg[ch.first_rank];
+      a.part_seg[2 * (base + c) + 1] = a.rank_seg[ch.last_rank];
+    }
+  }
+}
+
+// is row r in the protected list?
+template <class P>
+__device__ __forceinline__ void plan_row(const AttendArgs& a, int64_t r, P prot, int n_prot) {
+  const int lo = lower_bound_i32(prot, n_prot, r);
+  a.row_src[r] = (lo < n_prot && prot[lo] == r) ? 1 : 0;
+}
+
+__global__ __launch_bounds__(256) void plan_slots_kernel(AttendArgs a) {
+  const int64_t n_slots = a.dyn != nullptr ? a.dyn->n_slots : a.n_slots;
+  const int64_t n_parts = a.dyn != nullptr ? a.dyn->n_parts : a.n_parts;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= n_slots;
+       i += (int64_t)gridDim.x * blockDim.x)
+    plan_slot(a, i, n_slots, n_parts, [&](int64_t r) { return segment_of_row(a, r); });
+}
+
+__global__ __launch_bounds__(256) void row_src_kernel(AttendArgs a) {
+  const int n_prot = a.dyn != nullptr ? a.dyn->n_prot : a.n_prot;
+  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < a.n_rows;
+       r += (int64_t)gridDim.x * blockDim.x)
+    plan_row(a, r, a.prot, n_prot);
+}
+
+// part_ptr / part_seg (when part_ptr is set) and row_src (when set); grids cover
+// the host count of slots and rows (for a device plan, the capacity bound)
+hipError_t launch_plan(const AttendArgs& a, hipStream_t s) {
+  if (a.part_ptr != nullptr) {
+    const int64_t n = a.n_slots + 1;
+    const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, 8192);
+    plan_slots_kernel<<<dim3(blocks), dim3(256), 0, s>>>(a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (a.row_src == nullptr) return hipSuccess;
+  const unsigned rb = (unsigned)std::min<int64_t>((a.n_rows + 255) / 256, 4096);
+  row_src_kernel<<<dim3(rb), dim3(256), 0, s>>>(a);
   return hipGetLastError();
+}
+
+constexpr int64_t kPlanOneRows = 65536;
+constexpr int kPlanOneSegs = 512, kPlanOneGroups = 2048;
+
+// every phase of a device plan in one launch: workgroup 0 also leaves the counts
+// in device memory for the attention kernels
+__global__ __launch_bounds__(kPlanThreads) void dplan_one_kernel(DPlanArgs d, AttendArgs a) {
+  __shared__ int32_t s_lo[kPlanOneSegs], s_cnt[kPlanOneSegs], s_group[kPlanOneGroups + 1];
+  __shared__ int64_t s_base[kPlanOneSegs];
+  __shared__ int32_t s_kv[kPlanOneSegs], s_seg[kPlanOneSegs];   // in storage order
+  __shared__ int32_t s_prot[kPlanLdsRows];
+  __shared__ DynPlan s_dyn;
+  DPlanArgs p = d;
+  p.seg_prot_lo = s_lo;
+  p.seg_prot_cnt = s_cnt;
+  p.seg_local_base = s_base;
+  p.group_base = s_group;
+  p.dyn = &s_dyn;
+  if (blockIdx.x != 0) p.status_out = nullptr;
+  int32_t MLA_LDS* prot = (int32_t MLA_LDS*)s_prot;
+  if (threadIdx.x < d.n_segs) {   // at most kPlanOneSegs; read after the barriers of the count
+    const int sg = d.storage[threadIdx.x];
+    s_seg[threadIdx.x] = sg;
+    s_kv[threadIdx.x] = (int32_t)d.segs[sg].kv_start;
+  }
+  plan_count(p, prot);
+  __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x == 0) *d.dyn = s_dyn;
+  const int64_t first = (int64_t)blockIdx.x * kPlanThreads + threadIdx.x, stride = (int64_t)gridDim.x * kPlanThreads;
+  for (int64_t i = first; i < s_dyn.n_items; i += stride) plan_item(p, (int)i, d.items);
+  a.seg_prot_lo = s_lo;
+  a.seg_local_base = s_base;
+  const int32_t MLA_LDS* kv = (const int32_t MLA_LDS*)s_kv;
+  auto seg_of = [&](int64_t r) -> int {
+    int lo = 0, hi = d.n_segs - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (kv[mid] <= r) lo = mid; else hi = mid - 1;
+    }
+    return s_seg[lo];
+  };
+  if (a.part_ptr != nullptr)
+    for (int64_t i = first; i <= s_dyn.n_slots; i += stride) plan_slot(a, i, s_dyn.n_slots, s_dyn.n_parts, seg_of);
+  if (a.row_src != nullptr) {
+    const int np = s_dyn.n_prot;
+    for (int64_t r = first; r < a.n_rows; r += stride)
+      if (np <= kPlanLdsRows) plan_row(a, r, (const int32_t MLA_LDS*)prot, np); else plan_row(a, r, a.prot, np);
+  }
+}
+
+// d: the counts and items; a: the index and flags of the same call (a.dyn = d.dyn)
+hipError_t launch_dplan(const DPlanArgs& d, const AttendArgs& a, hipStream_t s) {
+  if (d.n_rows <= kPlanOneRows && d.n_segs <= kPlanOneSegs && d.n_item_groups <= kPlanOneGroups) {
+    int64_t n = std::max<int64_t>(d.max_items, 1);
+    if (a.part_ptr != nullptr) n = std::max(n, a.n_slots + 1);
+    if (a.row_src != nullptr) n = std::max(n, a.n_rows);
+    const unsigned blocks = (unsigned)std::min<int64_t>((n + kPlanThreads - 1) / kPlanThreads, 256);
+    dplan_one_kernel<<<dim3(blocks), dim3(kPlanThreads), 0, s>>>(d, a);
+    return hipGetLastError();
+  }
+  dplan_count_kernel<<<dim3(1), dim3(kPlanThreads), 0, s>>>(d);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (d.max_items > 0) {
+    dplan_items_kernel<<<dim3((unsigned)((d.max_items + 255) / 256)), dim3(256), 0, s>>>(d);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  return launch_plan(a, s);
 }
 
 }  // namespace mla
