@@ -552,7 +552,7 @@ mla_status mla_sliced_oproj_add(const mla_geom* geom, int64_t n_rows, const void
   a.n_pg = geom->n_proj_groups;
   for (int g = 0; g < geom->n_groups; ++g) a.glob_head[g] = glob_head[g];
   a.z_bf16 = 0;
-  hipError_t e = mla::launch_oproj(a, 3, reinterpret_cast<hipStream_t>(stream));
+  hipError_t e = mla::launch_oproj(a, reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "o-proj kernels");
   return MLA_OK;
 }
@@ -984,7 +984,7 @@ mla_status mla_sliced_oproj_add_planned(const mla_geom* geom, const mla_plan_inf
   a.n_pg = geom->n_proj_groups;
   a.z_bf16 = z_dtype == MLA_BF16 ? 1 : 0;
   for (int g = 0; g < geom->n_groups; ++g) a.glob_head[g] = glob_head[g];
-  const hipError_t e = mla::launch_oproj(a, 3, reinterpret_cast<hipStream_t>(stream));
+  const hipError_t e = mla::launch_oproj(a, reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "o-proj kernels");
   return MLA_OK;
 }

@@ -24,9 +24,9 @@ struct OprojArgs {
   int32_t glob_head[kMaxGroups];
 };
 
-// passes: bit 0 = Local heads over the protected rows, bit 1 = Global heads over all rows
-hipError_t launch_oproj(const OprojArgs& a, int passes, hipStream_t s);
-// grid size of one o-proj pass over M rows (the kernel indexes its tiles with int)
+// Global heads over all rows, then Local heads over the protected rows
+hipError_t launch_oproj(const OprojArgs& a, hipStream_t s);
+// grid size of an o-proj pass over M rows (the kernel indexes its tiles with int)
 int64_t oproj_workgroups(int64_t M, int d_model, int n_pg);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 // the producer's Local weights transposed: wt [n_pg, d_model/n_pg, K_L] bf16, K_L =

@@ -7,9 +7,8 @@
 //           z_off[r] on unprotected rows and nothing on protected rows, so
 //           z_off is never read for protected rows (the replace);
 //   pass L: rows a of the protected set, K = the Local heads of pg's groups;
-//           the result is added to the pass-G value in z[prot_rows[a]] (or, for
-//           the offline producer, which runs pass L alone, written there).
-// An epilogue loads the values it adds a 32-row block at a time, before the
+//           the result is added to the pass-G value in z[prot_rows[a]].
+// Pass G's epilogue loads the values it adds a 32-row block at a time, before the
 // block's first store, so that their latencies overlap.
 // Each head's weight rows are a d_c-row block of w_o[pg]; a K tile of 64 never
 // straddles two heads, so the B operand is gathered per tile by head.  The MFMAs
@@ -19,6 +18,7 @@
 #include "oproj.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace mla {
 
@@ -27,10 +27,10 @@ namespace mla {
 constexpr int OP_BK = 64;
 constexpr int OP_ALD = OP_BK + 8;     // padded A row (bf16): 144 B, conflict-free 16-byte row reads
 
-template <int PASS, int BM, int BN, int WM, int WN>   // PASS 0 = Local over protected rows, 1 = Global
+template <int BM, int BN, int WM, int WN>   // pass G
 // at most 128 registers per wave, so that two workgroups of 8 waves share a CU
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(4)))
-void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles, int local_add) {
+void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles) {
   constexpr int NT = WM * WN * 64;
   // padded B row: 2*BLD = 64 mod 256 bytes, so the four k-rows that each half-wave
   // of a transposing read touches land on disjoint 16-bank groups (all 64 banks)
@@ -75,27 +75,14 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles, int local_add) {
     const int d = *a.n_prot_dev;
     n_prot = d < 0 ? 0 : (d < a.n_prot ? d : a.n_prot);
   }
-  const int64_t M = PASS == 0 ? (int64_t)n_prot : a.n_rows;
-  if (m0 >= M) return;   // a tile past the device count of protected rows
-  const int heads_k = PASS == 0 ? gpp * (hpg - 1) : gpp;   // d_c-wide K blocks
-  const int K = heads_k * DC;
-  const uint16_t* A = (const uint16_t*)(PASS == 0 ? a.o_loc : a.o_glob);
-  const int64_t lda = PASS == 0 ? (int64_t)a.n_groups * (hpg - 1) * DC : (int64_t)a.n_groups * DC;
-  const int64_t acol = PASS == 0 ? (int64_t)pg * gpp * (hpg - 1) * DC : (int64_t)pg * gpp * DC;
+  const int64_t M = a.n_rows;
+  const int K = gpp * DC;   // one d_c-wide K block per Global head
+  const uint16_t* A = (const uint16_t*)a.o_glob;
+  const int64_t lda = (int64_t)a.n_groups * DC;
+  const int64_t acol = (int64_t)pg * gpp * DC;
   const uint16_t* W = (const uint16_t*)a.w_o + (int64_t)pg * heads_pp * DC * cw;
 
-  if (PASS == 0) {
-    for (int i = tid; i < OP_BM; i += NT) {
-      const int64_t m = m0 + i;
-      int orow = -1;
-      if (m < M) {
-        orow = a.prot_rows[m];
-        if (orow < 0 || orow >= a.n_rows) orow = -1;   // outside z: the row is skipped
-      }
-      row_flag[i] = 1;
-      row_out[i] = orow;
-    }
-  } else {
+  {
     // the tile's rows are [m0, m0 + BM): the protected ones are the run of the
     // sorted list between two lower bounds, found once per workgroup
     __shared__ int run[2];
@@ -122,14 +109,7 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles, int local_add) {
   // weight row of K index k (k is a multiple of 32 inside one head block)
   auto w_row = [&](int k) -> int64_t {
     const int kb = k / DC, d = k - kb * DC;
-    int hl;   // head index inside the projection group
-    if (PASS == 0) {
-      const int gl = kb / (hpg - 1), j = kb - gl * (hpg - 1);
-      const int gh = a.glob_head[pg * gpp + gl];
-      hl = gl * hpg + (j < gh ? j : j + 1);
-    } else {
-      hl = kb * hpg + a.glob_head[pg * gpp + kb];
-    }
+    const int hl = kb * hpg + a.glob_head[pg * gpp + kb];   // head inside the projection group
     return (int64_t)hl * DC + d;
   };
 
@@ -231,55 +211,33 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles, int local_add) {
   float MLA_LDS* stage = (float MLA_LDS*)As + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (32 * SLD);
   const uint16_t* zoff = (const uint16_t*)a.z_off;
   const int prow = elane >> 3, pc4 = (elane & 7) * 4;   // read-back: row prow + 8p, channels pc4 .. +3
-  // the values this block adds: pass G, bf16 z_off of the unprotected rows (none
-  // on protected rows); pass L after pass G, the row's z (f32 bits, or bf16)
-  const bool add_any = PASS == 1 || local_add != 0;
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
-    u32x4 addv[NI][4];
+    // the z_off this block adds (none on protected rows).  Every lane loads (element
+    // 0 where nothing is added) and the unused values are zeroed after: no branch
+    // around the loads, so each later wait counts exactly the loads still ahead of it.
+    // Widened to f32 here, so that the block's one wait for its loads comes before any
+    // of its stores (later waits would count those stores too).
     f32x4 addf[NI][4];
-    if (add_any) {
-      // every lane loads (element 0 where nothing is added) and the unused
-      // values are zeroed after: no branch around the loads, so each later wait
-      // counts exactly the loads still ahead of it
-      auto add_off = [&](int ni, int p, bool& use) -> int64_t {
-        const int n = n0 + wn * TN + ni * 32 + pc4;
-        const int r = wm * TM + mi * 32 + p * 8 + prow;
-        const int64_t orow = m0 + r < M && n < cw ? (int64_t)row_out[r] : -1;
-        use = orow >= 0 && (PASS == 0 || !row_flag[r]);
-        return use ? orow * a.d_model + (int64_t)pg * cw + n : 0;
-      };
-      if (PASS == 1 || a.z_bf16) {
-        const uint16_t* src = PASS == 1 ? zoff : (const uint16_t*)a.z;
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-          for (int p = 0; p < 4; ++p) {
-            bool use;
-            const u32x2 zz = *(const u32x2*)(src + add_off(ni, p, use));
-            addv[ni][p] = use ? u32x4{zz[0], zz[1], 0u, 0u} : u32x4{0u, 0u, 0u, 0u};
-          }
-      } else {
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-          for (int p = 0; p < 4; ++p) {
-            bool use;
-            const u32x4 w = *(const u32x4*)(a.z + add_off(ni, p, use));
-            addv[ni][p] = use ? w : u32x4{0u, 0u, 0u, 0u};
-          }
-      }
-      // widened to f32 here, so that the block's one wait for its loads comes
-      // before any of its stores (later waits would count those stores too)
+    {
+      u32x2 addv[NI][4];
 #pragma unroll
       for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-          const u32x4 w = addv[ni][p];
-          addf[ni][p] = PASS == 1 || a.z_bf16
-                            ? f32x4{bf16_lo(w[0]), bf16_hi(w[0]), bf16_lo(w[1]), bf16_hi(w[1])}
-                            : f32x4{__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]),
-                                    __uint_as_float(w[3])};
+          const int n = n0 + wn * TN + ni * 32 + pc4;
+          const int r = wm * TM + mi * 32 + p * 8 + prow;
+          const int64_t orow = m0 + r < M && n < cw ? (int64_t)row_out[r] : -1;
+          const bool use = orow >= 0 && !row_flag[r];
+          const u32x2 zz = *(const u32x2*)(zoff + (use ? orow * a.d_model + (int64_t)pg * cw + n : 0));
+          addv[ni][p] = use ? zz : u32x2{0u, 0u};
+        }
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const u32x2 w = addv[ni][p];
+          addf[ni][p] = f32x4{bf16_lo(w[0]), bf16_hi(w[0]), bf16_lo(w[1]), bf16_hi(w[1])};
         }
     }
 #pragma unroll
@@ -298,7 +256,7 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles, int local_add) {
         const int64_t orow = row_out[r];
         if (orow < 0) continue;
         const int64_t off = orow * a.d_model + (int64_t)pg * cw + n;
-        if (add_any) v += addf[ni][p];
+        v += addf[ni][p];
         if (a.z_bf16)
           *(u32x2*)((uint16_t*)a.z + off) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
         else
@@ -306,6 +264,268 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles, int local_add) {
       }
     }
   }
+}
+
+// Pass L on the W_b kernel's plan (wb.hip): tiles of 32 MI protected rows x 256
+// channels, 8 waves of 16 MI x 64, operands by direct global->LDS loads 64 of K at a
+// time into NST slices, the barrier between a step's halves.  The weight rows of a
+// slice are K-major: channel fragments come by transposing reads.  The tile height
+// follows the device's count of protected rows (the host only knows the capacity),
+// so one persistent workgroup per compute unit picks it and walks its tiles.
+//
+// At a few hundred protected rows the 256-row tiles of pass G left most of the chip
+// idle in a serial K loop of 56 round trips.  Pass L at 310 protected rows 75 -> 35
+// us, 2662 rows 129 -> 125, 16K rows with a rotary value 98 -> 73, 7291 rows 328 ->
+// 296 (64 heads); 4014 rows of 128 heads 300 -> 254.
+constexpr int OL_BN = 256, OL_WAVES = 8, OL_GRID = 256;
+constexpr int OL_LDS = 147456;                 // the largest variant's slices
+
+__device__ __forceinline__ void ol_dma16(const unsigned char* base, uint32_t voff, const unsigned char MLA_LDS* dst) {
+  const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)dst);
+  const uint64_t b = (uint64_t)(uintptr_t)base;
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint64_t bs = ((uint64_t)hi << 32) | (uint64_t)lo;
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :: "v"(voff), "s"(bs), "s"(m0) : "memory", "m0");
+}
+// all but the latest N of this wave's direct loads have landed and its LDS reads
+// are done; then all waves meet
+template <int N>
+__device__ __forceinline__ void ol_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
+}
+
+// weight row of K index k of projection group pg's Local heads
+__device__ __forceinline__ int local_w_row(const OprojArgs& a, int pg, int k) {
+  const int hpg = a.n_heads / a.n_groups, gpp = a.n_groups / a.n_pg;
+  const int kb = k / a.d_latent, d = k - kb * a.d_latent;
+  const int gl = kb / (hpg - 1), j = kb - gl * (hpg - 1);
+  const int gh = a.glob_head[pg * gpp + gl];
+  return (gl * hpg + (j < gh ? j : j + 1)) * a.d_latent + d;
+}
+
+template <int MI, int NST>
+__device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned char* lds) {
+  constexpr int NI = 4, BM = 32 * MI;
+  constexpr int A_BYTES = BM * 128, STAGE = A_BYTES + 64 * OL_BN * 2;
+  constexpr int NA = A_BYTES / 1024, NLOADS = STAGE / 1024, LPW = (NLOADS + OL_WAVES - 1) / OL_WAVES;
+  static_assert(NST * STAGE <= OL_LDS, "slices");
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hpg = a.n_heads / a.n_groups, gpp = a.n_groups / a.n_pg;
+  const int cw = a.d_model / a.n_pg, DC = a.d_latent;
+  const int K = gpp * (hpg - 1) * DC, nk = K / 64;
+  const int64_t lda = (int64_t)a.n_groups * (hpg - 1) * DC;
+  const int m_tiles = (M + BM - 1) / BM, n_tiles = (cw + OL_BN - 1) / OL_BN;
+  // XCD x takes a contiguous range of tiles, row tiles innermost: neighbours share
+  // a weight panel in its L2
+  const int total = m_tiles * n_tiles * a.n_pg, per = (total + 7) / 8;
+  const int wm = wave >> 2, wn = wave & 3, lg = lane >> 4, lc = lane & 15;
+
+  for (int ti = (int)(blockIdx.x / 8); ti < per; ti += OL_GRID / 8) {
+    int tb = (int)(blockIdx.x % 8) * per + ti;
+    if (tb >= total) break;
+    const int mt = tb % m_tiles;
+    tb /= m_tiles;
+    const int nt = tb % n_tiles, pg = tb / n_tiles;
+    const int m0 = mt * BM, n0 = nt * OL_BN;
+    const unsigned char* A = (const unsigned char*)((const uint16_t*)a.o_loc + (int64_t)pg * K);
+    const unsigned char* W = (const unsigned char*)((const uint16_t*)a.w_o + (int64_t)pg * (a.n_heads / a.n_pg) * DC * cw);
+
+    // direct loads: load q fills LDS bytes [1024 q, +1024) of a stage.  q < NA: 8 rows
+    // of the A slice, chunk c of row r at c ^ ((r >> 1) & 7), rows past the end repeat
+    // the last.  The rest: two weight rows k of 256 channels, chunk c at c ^ 2 g(k),
+    // g(k) = k % 4 + 4 (k / 8 % 2): the 8 rows a half-wave of a transposing read
+    // touches hit distinct 32-byte bank groups; channels past the end repeat the last.
+    const unsigned char* src[LPW];
+    uint32_t voff[LPW];
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) {
+      const int q = std::min(wave + OL_WAVES * j, NLOADS - 1);
+      if (q < NA) {
+        const int r0 = 8 * q, lr = lane >> 3;
+        const int first = std::min(r0, M - 1 - m0), row = std::min(r0 + lr, M - 1 - m0);
+        src[j] = A + (int64_t)(m0 + first) * lda * 2;
+        voff[j] = (uint32_t)((row - first) * lda * 2 + ((lane & 7) ^ (((r0 + lr) >> 1) & 7)) * 16);
+      } else {
+        const int k = 2 * (q - NA) + (lane >> 5);
+        const int c = (lane & 31) ^ (2 * ((k & 3) | ((k >> 1) & 4)));
+        src[j] = W;
+        voff[j] = (uint32_t)(k * cw + std::min(n0 + c * 8, cw - 8)) * 2u;
+      }
+    }
+    auto load_one = [&](int j, int kt, int64_t wk, int st) {
+      const int q = std::min(wave + OL_WAVES * j, NLOADS - 1);
+      ol_dma16(src[j] + (q < NA ? (int64_t)kt * 128 : wk), voff[j], (const unsigned char MLA_LDS*)(lds + st + 1024 * q));
+    };
+    // byte offset of the next slice's first weight row: a slice never straddles two
+    // heads, whose rows are consecutive
+    int w_kt = 0, w_left = 0;
+    int64_t w_at = 0;
+    const int64_t w_step = (int64_t)64 * cw * 2;
+    auto next_w = [&]() -> int64_t {
+      if (w_left == 0) {
+        w_at = (int64_t)local_w_row(a, pg, w_kt * 64) * cw * 2;
+        w_left = DC / 64;
+      } else {
+        w_at += w_step;
+      }
+      --w_left;
+      ++w_kt;
+      return w_at;
+    };
+
+    f32x4 acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    struct Frags {
+      bf16x8 a[MI], b[NI];
+    };
+    const unsigned char MLA_LDS* L = (const unsigned char MLA_LDS*)lds;
+    const int fa = (wm * (BM / 2) + lc) * 128 + ((lg ^ ((lc >> 1) & 7)) * 16);
+    const int rr = (lane >> 2) & 3, cb = lane & 3;
+    const int fb = A_BYTES + (lg * 8 + rr) * (OL_BN * 2) + (((wn * 8 + (cb >> 1)) ^ (2 * (rr | ((lg & 1) << 2)))) * 16) + (cb & 1) * 8;
+    auto frag_a = [&](int st, int h, int i) -> bf16x8 { return *(const bf16x8 MLA_LDS*)(L + ((st + fa) ^ (h * 64)) + i * 2048); };
+    auto frag_b = [&](int st, int h, int j) -> bf16x8 {
+      const unsigned char MLA_LDS* p = L + ((st + fb) ^ (j * 32)) + h * (32 * OL_BN * 2);
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((MLA_LDS bf16x4*)p);
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((MLA_LDS bf16x4*)(p + 4 * OL_BN * 2));
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    auto half = [&](const Frags& f, Frags& nx, int nst, int nh, auto LOAD, int kt, int64_t wk, int lst) {
+      constexpr int R = MI + NI, PER = (R + MI - 1) / MI;
+      int rd = 0, ld = 0;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k, ++rd)
+          if (rd < NI) nx.b[rd] = frag_b(nst, nh, rd);
+          else if (rd < R) nx.a[rd - NI] = frag_a(nst, nh, rd - NI);
+        if constexpr (decltype(LOAD)::value) {
+#pragma unroll
+          for (int k = 0; k < (LPW + MI - 1) / MI; ++k, ++ld)
+            if (ld < LPW) load_one(ld, kt, wk, lst);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int jj = 0; jj < NI; ++jj) {
+          const int j = i & 1 ? NI - 1 - jj : jj;
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.b[j], f.a[i], acc[i][j], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+#pragma unroll
+    for (int p = 0; p < NST; ++p)
+      if (p < nk) {
+        const int64_t wk = next_w();
+#pragma unroll
+        for (int j = 0; j < LPW; ++j) load_one(j, p, wk, p * STAGE);
+      }
+    if (nk >= NST) ol_barrier<(NST - 1) * LPW>(); else ol_barrier<0>();
+    Frags f0, f1;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) f0.b[j] = frag_b(0, 0, j);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) f0.a[i] = frag_a(0, 0, i);
+    int st = 0, kt = 0;
+    for (; kt + NST < nk; ++kt) {
+      const int64_t wk = next_w();
+      half(f0, f1, st, 1, std::false_type{}, 0, 0, 0);
+      ol_barrier<(NST - 2) * LPW>();
+      const int nst = st == (NST - 1) * STAGE ? 0 : st + STAGE;
+      half(f1, f0, nst, 0, std::true_type{}, kt + NST, wk, st);
+      st = nst;
+    }
+    for (; kt < nk; ++kt) {
+      half(f0, f1, st, 1, std::false_type{}, 0, 0, 0);
+      ol_barrier<0>();
+      const int nst = st == (NST - 1) * STAGE ? 0 : st + STAGE;
+      half(f1, f0, nst, 0, std::false_type{}, 0, 0, 0);   // after the last slice: stale, not used
+      st = nst;
+    }
+
+    // epilogue: 16 rows x 64 channels a wave at a time through LDS (16-byte chunk c of
+    // row r at c ^ (r & 7)), read back row-contiguous; the row's z is added in f32
+    int orow[MI][4];
+    const int rl = lane >> 4, cl = lane & 15;
+    const int n = n0 + wn * 64 + cl * 4;   // cw is a multiple of 32
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const int m = m0 + wm * (BM / 2) + i * 16 + p * 4 + rl;
+        const int r = a.prot_rows[std::min(m, M - 1)];
+        orow[i][p] = m < M && n < cw && r >= 0 && r < a.n_rows ? r : -1;   // outside z: skipped
+      }
+    ol_barrier<0>();
+    unsigned char MLA_LDS* sw = (unsigned char MLA_LDS*)lds + wave * 8192;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      f32x4 old[4];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const int64_t off = orow[i][p] >= 0 ? (int64_t)orow[i][p] * a.d_model + (int64_t)pg * cw + n : 0;
+        if (a.z_bf16) {
+          const u32x2 w = *(const u32x2*)((const uint16_t*)a.z + off);
+          old[p] = f32x4{bf16_lo(w[0]), bf16_hi(w[0]), bf16_lo(w[1]), bf16_hi(w[1])};
+        } else {
+          old[p] = *(const f32x4*)(a.z + off);
+        }
+      }
+      unsigned char MLA_LDS* sb = sw + (i & 1) * 4096;
+#pragma unroll
+      for (int j = 0; j < NI; ++j) *(f32x4 MLA_LDS*)(sb + lc * 256 + (((j * 4 + lg) ^ (lc & 7)) * 16)) = acc[i][j];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const int r = p * 4 + rl;
+        f32x4 v = *(const f32x4 MLA_LDS*)(sb + r * 256 + ((cl ^ (r & 7)) * 16));
+        if (orow[i][p] < 0) continue;
+        v += old[p];
+        const int64_t off = (int64_t)orow[i][p] * a.d_model + (int64_t)pg * cw + n;
+        if (a.z_bf16)
+          *(u32x2*)((uint16_t*)a.z + off) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+        else
+          *(f32x4*)(a.z + off) = v;
+      }
+    }
+    ol_barrier<0>();   // the next tile's slices may come in
+  }
+}
+
+__global__ __launch_bounds__(OL_WAVES * 64, 2) void oproj_local_kernel(OprojArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[OL_LDS];
+  // protected rows in use: the host count, or the device count clamped to the capacity
+  int M = a.n_prot;
+  if (a.n_prot_dev != nullptr) {
+    const int d = *a.n_prot_dev;
+    M = d < 0 ? 0 : (d < M ? d : M);
+  }
+  if (M == 0) return;
+  const int cw = a.d_model / a.n_pg;
+  const int64_t n_tiles = (int64_t)((cw + OL_BN - 1) / OL_BN) * a.n_pg;
+  // tile height as in wb.hip: rounds over the chip, a tile of 32 mi rows taken as mi + 3
+  int best = 8;
+  int64_t cost = INT64_MAX;
+#pragma unroll
+  for (int mi = 8; mi >= 1; mi >>= 1) {
+    const int64_t c = (((int64_t)M + 32 * mi - 1) / (32 * mi) * n_tiles + OL_GRID - 1) / OL_GRID * (mi + 3);
+    if (c < cost) {
+      cost = c;
+      best = mi;
+    }
+  }
+  best = __builtin_amdgcn_readfirstlane(best);
+  if (best == 1)
+    local_tiles<1, 4>(a, M, lds);
+  else if (best == 2)
+    local_tiles<2, 3>(a, M, lds);
+  else if (best == 4)
+    local_tiles<4, 3>(a, M, lds);
+  else
+    local_tiles<8, 2>(a, M, lds);
 }
 
 // W_{a,L}^T of each projection group, for the producer's Local projection as a
@@ -385,26 +605,20 @@ int64_t oproj_workgroups(int64_t M, int d_model, int n_pg) {
   return 8 * ((tiles + 7) / 8);
 }
 
-template <int PASS>
-hipError_t launch_pass(const OprojArgs& a, int64_t M, int local_add, hipStream_t s) {
-  constexpr int BM = kOpBM, BN = kOpBN, WM = kOpWM, WN = kOpWN;
-  const int cw = a.d_model / a.n_pg;
-  const int n_tiles = (cw + BN - 1) / BN;
-  const int m_tiles = (int)((M + BM - 1) / BM);
-  const int total = m_tiles * n_tiles * a.n_pg;
-  oproj_kernel<PASS, BM, BN, WM, WN><<<dim3((unsigned)(8 * ((total + 7) / 8))), dim3(WM * WN * 64), 0, s>>>(
-      a, m_tiles, n_tiles, local_add);
-  return hipGetLastError();
-}
-
-hipError_t launch_oproj(const OprojArgs& a, int passes, hipStream_t s) {
-  const int hpg = a.n_heads / a.n_groups;
-  if ((passes & 2) && a.n_rows > 0) {
-    const hipError_t e = launch_pass<1>(a, a.n_rows, 0, s);
+hipError_t launch_oproj(const OprojArgs& a, hipStream_t s) {
+  if (a.n_rows > 0) {
+    const int cw = a.d_model / a.n_pg;
+    const int n_tiles = (cw + kOpBN - 1) / kOpBN, m_tiles = (int)((a.n_rows + kOpBM - 1) / kOpBM);
+    const int total = m_tiles * n_tiles * a.n_pg;
+    oproj_kernel<kOpBM, kOpBN, kOpWM, kOpWN><<<dim3((unsigned)(8 * ((total + 7) / 8))), dim3(kOpWM * kOpWN * 64), 0, s>>>(
+        a, m_tiles, n_tiles);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  // after pass G the Local values add to z; alone (the producer) they are written
-  if ((passes & 1) && a.n_prot > 0 && hpg > 1) return launch_pass<0>(a, a.n_prot, (passes & 2) ? 1 : 0, s);
+  if (a.n_prot > 0 && a.n_heads > a.n_groups) {
+    oproj_local_kernel<<<dim3(OL_GRID), dim3(OL_WAVES * 64), 0, s>>>(a);
+    return hipGetLastError();
+  }
   return hipSuccess;
 }
 
