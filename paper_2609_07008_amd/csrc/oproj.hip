@@ -266,18 +266,18 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles) {
   }
 }
 
-// Pass L on the W_b kernel's plan (wb.hip): tiles of 32 MI protected rows x 256
-// channels, 8 waves of 16 MI x 64, operands by direct global->LDS loads 64 of K at a
+// Pass L on the W_b kernel's plan (wb.hip): tiles of 32 MI protected rows x BN
+// channels, 8 waves of 16 MI x BN / 4, operands by direct global->LDS loads 64 of K at a
 // time into NST slices, the barrier between a step's halves.  The weight rows of a
-// slice are K-major: channel fragments come by transposing reads.  The tile height
+// slice are K-major: channel fragments come by transposing reads.  The tile
 // follows the device's count of protected rows (the host only knows the capacity),
 // so one persistent workgroup per compute unit picks it and walks its tiles.
 //
 // At a few hundred protected rows the 256-row tiles of pass G left most of the chip
-// idle in a serial K loop of 56 round trips.  Pass L at 310 protected rows 75 -> 35
+// idle in a serial K loop of 56 round trips.  Pass L at 310 protected rows 75 -> 25
 // us, 2662 rows 129 -> 125, 16K rows with a rotary value 98 -> 73, 7291 rows 328 ->
 // 296 (64 heads); 4014 rows of 128 heads 300 -> 254.
-constexpr int OL_BN = 256, OL_WAVES = 8, OL_GRID = 256;
+constexpr int OL_WAVES = 8, OL_GRID = 256;
 constexpr int OL_LDS = 147456;                 // the largest variant's slices
 
 __device__ __forceinline__ void ol_dma16(const unsigned char* base, uint32_t voff, const unsigned char MLA_LDS* dst) {
@@ -305,10 +305,12 @@ __device__ __forceinline__ int local_w_row(const OprojArgs& a, int pg, int k) {
   return (gl * hpg + (j < gh ? j : j + 1)) * a.d_latent + d;
 }
 
-template <int MI, int NST>
+// MI: 16-row blocks per wave, BN: channels per tile (a wave's share: BN / 4), NST: slices
+template <int MI, int BN, int NST>
 __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned char* lds) {
-  constexpr int NI = 4, BM = 32 * MI;
-  constexpr int A_BYTES = BM * 128, STAGE = A_BYTES + 64 * OL_BN * 2;
+  constexpr int NI = BN / 64, BM = 32 * MI;
+  constexpr int LPR = BN / 8;                  // lanes, and 16-byte chunks, of a weight row
+  constexpr int A_BYTES = BM * 128, STAGE = A_BYTES + 64 * BN * 2;
   constexpr int NA = A_BYTES / 1024, NLOADS = STAGE / 1024, LPW = (NLOADS + OL_WAVES - 1) / OL_WAVES;
   static_assert(NST * STAGE <= OL_LDS, "slices");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -316,7 +318,7 @@ __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned 
   const int cw = a.d_model / a.n_pg, DC = a.d_latent;
   const int K = gpp * (hpg - 1) * DC, nk = K / 64;
   const int64_t lda = (int64_t)a.n_groups * (hpg - 1) * DC;
-  const int m_tiles = (M + BM - 1) / BM, n_tiles = (cw + OL_BN - 1) / OL_BN;
+  const int m_tiles = (M + BM - 1) / BM, n_tiles = (cw + BN - 1) / BN;
   // XCD x takes a contiguous range of tiles, row tiles innermost: neighbours share
   // a weight panel in its L2
   const int total = m_tiles * n_tiles * a.n_pg, per = (total + 7) / 8;
@@ -328,13 +330,13 @@ __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned 
     const int mt = tb % m_tiles;
     tb /= m_tiles;
     const int nt = tb % n_tiles, pg = tb / n_tiles;
-    const int m0 = mt * BM, n0 = nt * OL_BN;
+    const int m0 = mt * BM, n0 = nt * BN;
     const unsigned char* A = (const unsigned char*)((const uint16_t*)a.o_loc + (int64_t)pg * K);
     const unsigned char* W = (const unsigned char*)((const uint16_t*)a.w_o + (int64_t)pg * (a.n_heads / a.n_pg) * DC * cw);
 
     // direct loads: load q fills LDS bytes [1024 q, +1024) of a stage.  q < NA: 8 rows
     // of the A slice, chunk c of row r at c ^ ((r >> 1) & 7), rows past the end repeat
-    // the last.  The rest: two weight rows k of 256 channels, chunk c at c ^ 2 g(k),
+    // the last.  The rest: weight rows k of BN channels, chunk c at c ^ 2 g(k),
     // g(k) = k % 4 + 4 (k / 8 % 2): the 8 rows a half-wave of a transposing read
     // touches hit distinct 32-byte bank groups; channels past the end repeat the last.
     const unsigned char* src[LPW];
@@ -348,8 +350,8 @@ __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned 
         src[j] = A + (int64_t)(m0 + first) * lda * 2;
         voff[j] = (uint32_t)((row - first) * lda * 2 + ((lane & 7) ^ (((r0 + lr) >> 1) & 7)) * 16);
       } else {
-        const int k = 2 * (q - NA) + (lane >> 5);
-        const int c = (lane & 31) ^ (2 * ((k & 3) | ((k >> 1) & 4)));
+        const int k = 64 / LPR * (q - NA) + lane / LPR;
+        const int c = (lane % LPR) ^ (2 * ((k & 3) | ((k >> 1) & 4)));
         src[j] = W;
         voff[j] = (uint32_t)(k * cw + std::min(n0 + c * 8, cw - 8)) * 2u;
       }
@@ -386,12 +388,12 @@ __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned 
     const unsigned char MLA_LDS* L = (const unsigned char MLA_LDS*)lds;
     const int fa = (wm * (BM / 2) + lc) * 128 + ((lg ^ ((lc >> 1) & 7)) * 16);
     const int rr = (lane >> 2) & 3, cb = lane & 3;
-    const int fb = A_BYTES + (lg * 8 + rr) * (OL_BN * 2) + (((wn * 8 + (cb >> 1)) ^ (2 * (rr | ((lg & 1) << 2)))) * 16) + (cb & 1) * 8;
+    const int fb = A_BYTES + (lg * 8 + rr) * (BN * 2) + (((wn * (2 * NI) + (cb >> 1)) ^ (2 * (rr | ((lg & 1) << 2)))) * 16) + (cb & 1) * 8;
     auto frag_a = [&](int st, int h, int i) -> bf16x8 { return *(const bf16x8 MLA_LDS*)(L + ((st + fa) ^ (h * 64)) + i * 2048); };
     auto frag_b = [&](int st, int h, int j) -> bf16x8 {
-      const unsigned char MLA_LDS* p = L + ((st + fb) ^ (j * 32)) + h * (32 * OL_BN * 2);
+      const unsigned char MLA_LDS* p = L + ((st + fb) ^ (j * 32)) + h * (32 * BN * 2);
       const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((MLA_LDS bf16x4*)p);
-      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((MLA_LDS bf16x4*)(p + 4 * OL_BN * 2));
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((MLA_LDS bf16x4*)(p + 4 * BN * 2));
       return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
     auto half = [&](const Frags& f, Frags& nx, int nst, int nh, auto LOAD, int kt, int64_t wk, int lst) {
@@ -447,16 +449,17 @@ __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned 
       st = nst;
     }
 
-    // epilogue: 16 rows x 64 channels a wave at a time through LDS (16-byte chunk c of
+    // epilogue: 16 rows x BN / 4 channels a wave at a time through LDS (16-byte chunk c of
     // row r at c ^ (r & 7)), read back row-contiguous; the row's z is added in f32
-    int orow[MI][4];
-    const int rl = lane >> 4, cl = lane & 15;
-    const int n = n0 + wn * 64 + cl * 4;   // cw is a multiple of 32
+    constexpr int CPR = 4 * NI, RPP = 64 / CPR, NP = 16 / RPP;   // chunks of a row, rows a pass, passes
+    int orow[MI][NP];
+    const int rl = lane / CPR, cl = lane % CPR;
+    const int n = n0 + wn * (16 * NI) + cl * 4;   // cw is a multiple of 32
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const int m = m0 + wm * (BM / 2) + i * 16 + p * 4 + rl;
+      for (int p = 0; p < NP; ++p) {
+        const int m = m0 + wm * (BM / 2) + i * 16 + p * RPP + rl;
         const int r = a.prot_rows[std::min(m, M - 1)];
         orow[i][p] = m < M && n < cw && r >= 0 && r < a.n_rows ? r : -1;   // outside z: skipped
       }
@@ -464,9 +467,9 @@ __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned 
     unsigned char MLA_LDS* sw = (unsigned char MLA_LDS*)lds + wave * 8192;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      f32x4 old[4];
+      f32x4 old[NP];
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
+      for (int p = 0; p < NP; ++p) {
         const int64_t off = orow[i][p] >= 0 ? (int64_t)orow[i][p] * a.d_model + (int64_t)pg * cw + n : 0;
         if (a.z_bf16) {
           const u32x2 w = *(const u32x2*)((const uint16_t*)a.z + off);
@@ -477,11 +480,11 @@ __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned 
       }
       unsigned char MLA_LDS* sb = sw + (i & 1) * 4096;
 #pragma unroll
-      for (int j = 0; j < NI; ++j) *(f32x4 MLA_LDS*)(sb + lc * 256 + (((j * 4 + lg) ^ (lc & 7)) * 16)) = acc[i][j];
+      for (int j = 0; j < NI; ++j) *(f32x4 MLA_LDS*)(sb + lc * (16 * CPR) + (((j * 4 + lg) ^ (lc & 7)) * 16)) = acc[i][j];
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const int r = p * 4 + rl;
-        f32x4 v = *(const f32x4 MLA_LDS*)(sb + r * 256 + ((cl ^ (r & 7)) * 16));
+      for (int p = 0; p < NP; ++p) {
+        const int r = p * RPP + rl;
+        f32x4 v = *(const f32x4 MLA_LDS*)(sb + r * (16 * CPR) + ((cl ^ (r & 7)) * 16));
         if (orow[i][p] < 0) continue;
         v += old[p];
         const int64_t off = (int64_t)orow[i][p] * a.d_model + (int64_t)pg * cw + n;
@@ -505,27 +508,39 @@ __global__ __launch_bounds__(OL_WAVES * 64, 2) void oproj_local_kernel(OprojArgs
   }
   if (M == 0) return;
   const int cw = a.d_model / a.n_pg;
-  const int64_t n_tiles = (int64_t)((cw + OL_BN - 1) / OL_BN) * a.n_pg;
-  // tile height as in wb.hip: rounds over the chip, a tile of 32 mi rows taken as mi + 3
+  const int64_t n256 = (int64_t)((cw + 255) / 256) * a.n_pg, n128 = (int64_t)((cw + 127) / 128) * a.n_pg;
+  // The tile whose rounds over the chip cost least.  Heights 32 mi of 256 channels as
+  // in wb.hip, a tile taken as mi + 3 (here in thirds).  While a round is not full a
+  // compute unit's direct loads are what a slice waits for, so tiles of 128 channels,
+  // 20 or 24 KB a slice against 36 for 32 x 256: at K = 3584, 4096 channels 19.7 and
+  // 21.8 us against 30.8 at 32 rows, and 64 x 128 25 against 33 at 310 (two rounds of
+  // 32 x 128: 38), 27 against 36 at 512; at 600 rows 64 x 128 takes two rounds, 45,
+  // and 64 x 256 one, 38.
   int best = 8;
   int64_t cost = INT64_MAX;
-#pragma unroll
-  for (int mi = 8; mi >= 1; mi >>= 1) {
-    const int64_t c = (((int64_t)M + 32 * mi - 1) / (32 * mi) * n_tiles + OL_GRID - 1) / OL_GRID * (mi + 3);
+  auto tile = [&](int id, int bm, int64_t nt, int w) {
+    const int64_t c = (((int64_t)M + bm - 1) / bm * nt + OL_GRID - 1) / OL_GRID * w;
     if (c < cost) {
       cost = c;
-      best = mi;
+      best = id;
     }
-  }
+  };
+  tile(8, 256, n256, 33);
+  tile(4, 128, n256, 21);
+  tile(2, 64, n256, 15);
+  tile(12, 64, n128, 9);
+  tile(11, 32, n128, 8);
   best = __builtin_amdgcn_readfirstlane(best);
-  if (best == 1)
-    local_tiles<1, 4>(a, M, lds);
+  if (best == 11)
+    local_tiles<1, 128, 7>(a, M, lds);
+  else if (best == 12)
+    local_tiles<2, 128, 6>(a, M, lds);
   else if (best == 2)
-    local_tiles<2, 3>(a, M, lds);
+    local_tiles<2, 256, 3>(a, M, lds);
   else if (best == 4)
-    local_tiles<4, 3>(a, M, lds);
+    local_tiles<4, 256, 3>(a, M, lds);
   else
-    local_tiles<8, 2>(a, M, lds);
+    local_tiles<8, 256, 2>(a, M, lds);
 }
 
 // W_{a,L}^T of each projection group, for the producer's Local projection as a
@@ -596,7 +611,7 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
 // 256 x 128 tiles, 8 waves (4 x 2 wave tiles of 64 x 64): 58 KB of LDS and up to
 // 128 registers per wave, two workgroups per CU.  Same per-element K order as any
 // other tile shape, so the results do not depend on it.  At 256K the step's two
-// passes take 3.16 ms (128 x 256 the same; 256 x 256 with one workgroup per CU
+// passes, when both ran on such tiles, took 3.16 ms (128 x 256 the same; 256 x 256 with one workgroup per CU
 // 3.58, 64 x 256 with three 3.39, 128 x 128 with four 4.03 ms).
 constexpr int kOpBM = 256, kOpBN = 128, kOpWM = 4, kOpWN = 2;
 

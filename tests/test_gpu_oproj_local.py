@@ -1,5 +1,6 @@
-"""The o-proj's Local pass at each of its tile heights (32, 64, 128, 256 rows: picked
-by how the protected rows fill the compute units) and around their edges, with
+"""The o-proj's Local pass at each of its tiles (64, 128, 256 rows of 256 channels, 32
+and 64 rows of 128: picked by how the protected rows fill the compute units) and
+around their edges, with
 projection groups of 512, 448 and 96 channels (whole, ragged and part column
 tiles), dense and sliced, head widths of 64, 512 and 576, f32 and bf16 z, and a
 device count below the capacity.  Reference: z_online of eq:offonline in float64
@@ -22,7 +23,9 @@ def geom(H, G, d_c, d_r, d_model, n_pg, rotary=False):
 # geometry, rows, protected rows
 CASES = {
     "height32_one_row": (geom(64, 8, 512, 64, 4096, 8), 300, 1),
-    "height32": (geom(64, 8, 512, 64, 4096, 8), 700, 511),
+    "height32": (geom(64, 8, 512, 64, 4096, 8), 300, 255),
+    "height64_narrow": (geom(64, 8, 512, 64, 4096, 8), 700, 511),
+    "height64_narrow_edge": (geom(64, 8, 512, 64, 4096, 8), 700, 257),
     "height64": (geom(64, 8, 512, 64, 4096, 8), 1100, 1023),
     "height128": (geom(64, 8, 512, 64, 4096, 8), 2100, 1030),
     "height256": (geom(64, 8, 512, 64, 4096, 8), 2500, 2400),
