@@ -22,10 +22,9 @@
 //                   R^-1: Alg. 2, eq:offonline)
 // and emits one normalized partial and one log-sum-exp per (slot, chunk), or,
 // with one chunk per slot, the merged head output itself.
-// Tiles are fetched with 16-byte direct-to-LDS loads (global_load_lds_dwordx4, in
-// attend.h), double-buffered; the
-// 16-byte chunks of a key row are XOR-swizzled so row and column reads hit
-// distinct banks.
+// Tiles are fetched with 16-byte direct-to-LDS loads (global_load_lds_dwordx4),
+// double-buffered; the 16-byte chunks of a key row are XOR-swizzled so row and
+// column reads hit distinct banks.
 #include "attend.h"
 
 namespace mla {
