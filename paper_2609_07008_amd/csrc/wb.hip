@@ -4,8 +4,8 @@
 // K-contiguous, so this is C = A B^T with A = z, B = W_b, on bf16 MFMA with fp32
 // accumulation; y is written in fp32 or bf16.
 //
-// Tiles of 32 MI rows x 256 channels per workgroup of 8 waves (2 x 4, each 16 MI x
-// 64); the operands come in by direct global->LDS loads, 64 of K at a time, NST
+// Tiles of 32 MI rows x BN channels (256; 128 at up to about 1000 rows) per workgroup
+// of 8 waves (2 x 4, each 16 MI x BN / 4); the operands come in by direct global->LDS loads, 64 of K at a time, NST
 // slices in LDS.  On a full chip power is what bounds it: 16x16x32 MFMAs take less
 // per flop than 32x32x16 (see attend_pair.hip), so a wave's 16-row fragments feed
 // MI x 4 of them, neighbours sharing an operand.  What stalls it otherwise is the
@@ -19,7 +19,7 @@
 // 2 or 16 7-14 %).
 //
 // 264,192 rows, 4096 -> 4096: bf16 y 7.10 -> 6.37 ms (1.39 PFLOP/s), f32 y 7.40 ->
-// 6.86; 2100 rows f32 81 -> 66 us, 300 rows 76 -> 30, 16 rows 72 -> 12.
+// 6.86; 2100 rows f32 81 -> 66 us, 300 rows 76 -> 21, 16 rows 72 -> 12.
 #include "wb.h"
 
 #include <algorithm>
@@ -28,10 +28,10 @@
 namespace mla {
 namespace {
 
-constexpr int WB_BN = 256, WB_BK = 64;
-constexpr int WB_WAVES = 8;                           // 2 x 4 waves of (BM/2) x 64
+constexpr int WB_BK = 64;
+constexpr int WB_WAVES = 8;                           // 2 x 4 waves of (BM/2) x (BN/4)
 constexpr int WB_ROWB = WB_BK * 2;                    // bytes of one row of a slice
-constexpr int64_t kWbFewRows = 64;
+constexpr int64_t kWbFewRows = 32;
 constexpr int WB_GM = 8;                              // row panels per column panel in the tile walk
 
 __device__ __forceinline__ void wb_dma16(const void* base, uint32_t voff, const unsigned char MLA_LDS* dst) {
@@ -53,11 +53,11 @@ __device__ __forceinline__ void wb_barrier() {
 
 __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
-// MI: 16-row blocks per wave (tile of 32 MI rows x 256 channels); NST: K slices in LDS
-template <bool OUT_BF16, int MI, int NST>
+// MI: 16-row blocks per wave (tile of 32 MI rows x BN channels); NST: K slices in LDS
+template <bool OUT_BF16, int MI, int BN, int NST>
 __global__ __launch_bounds__(WB_WAVES * 64, 2) void wb_gemm_kernel(WbArgs a, int m_tiles, int n_tiles, bool stream_out) {
-  constexpr int NI = 4, BM = 32 * MI;
-  constexpr int A_BYTES = BM * WB_ROWB, STAGE = A_BYTES + WB_BN * WB_ROWB;
+  constexpr int NI = BN / 64, BM = 32 * MI;
+  constexpr int A_BYTES = BM * WB_ROWB, STAGE = A_BYTES + BN * WB_ROWB;
   constexpr int NLOADS = STAGE / 1024;                       // 1 KB direct loads (8 rows each) per slice
   constexpr int LPW = (NLOADS + WB_WAVES - 1) / WB_WAVES;    // per wave; past the end the last one again
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(WB_WAVES * 64, 2) void wb_gemm_kernel(WbArgs a, int
   const int gm = std::min(WB_GM, m_tiles - group * WB_GM);
   const int mt = group * WB_GM + rem % gm, nt = rem / gm;
   const int64_t m0 = (int64_t)mt * BM;
-  const int n0 = nt * WB_BN;
+  const int n0 = nt * BN;
 
   // Direct loads: load q of a slice fills LDS bytes [1024 q, +1024) of the stage, the
   // slice's A rows then its B rows, 8 rows each; row r's chunk c sits at slot c ^
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(WB_WAVES * 64, 2) void wb_gemm_kernel(WbArgs a, int
   // rows' swizzle repeats every 16, so blocks are immediate offsets
   const int wm = wave >> 2, wn = wave & 3, lg = lane >> 4, lc = lane & 15;
   const int fa = (wm * (BM / 2) + lc) * WB_ROWB + ((lg ^ swz(lc)) * 16);
-  const int fb = A_BYTES + (wn * 64 + lc) * WB_ROWB + ((lg ^ swz(lc)) * 16);
+  const int fb = A_BYTES + (wn * (BN / 4) + lc) * WB_ROWB + ((lg ^ swz(lc)) * 16);
   struct Frags {
     bf16x8 a[MI], b[NI];
   };
@@ -178,19 +178,20 @@ __global__ __launch_bounds__(WB_WAVES * 64, 2) void wb_gemm_kernel(WbArgs a, int
     st = nst;
   }
 
-  // Epilogue through LDS, 16 rows x 64 channels a wave at a time: written in the
+  // Epilogue through LDS, 16 rows x BN / 4 channels a wave at a time: written in the
   // accumulator layout (row lc, channels lg*4 .. +3 of each block; 16-byte chunk c
-  // of row r at c ^ (r & 7)), read back row-contiguous, so that each store writes
+  // of row r at c ^ (r & SW)), read back row-contiguous, so that each store writes
   // whole 128-byte lines.
   wb_barrier<0>();
-  constexpr int ES = OUT_BF16 ? 2 : 4, ROW = 64 * ES;   // element and row bytes
+  constexpr int ES = OUT_BF16 ? 2 : 4, ROW = BN / 4 * ES;   // element and row bytes
   constexpr int CH = ROW / 16, RPI = 64 / CH;           // 16-byte chunks a row, rows a store
+  constexpr int SW = CH < 8 ? CH - 1 : 7;
   unsigned char MLA_LDS* sw = (unsigned char MLA_LDS*)lds + wave * (2 * 16 * ROW);
   const int64_t ybase = bt * a.y_batch;
   // whole chunks: y is 16-byte aligned
   const bool vec = ((a.ldy | a.y_batch) & (16 / ES - 1)) == 0;
   const int rl = lane / CH, cl = lane % CH;
-  const int n = n0 + wn * 64 + cl * (16 / ES);
+  const int n = n0 + wn * (BN / 4) + cl * (16 / ES);
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     unsigned char MLA_LDS* sb = sw + (i & 1) * (16 * ROW);
@@ -198,15 +199,15 @@ __global__ __launch_bounds__(WB_WAVES * 64, 2) void wb_gemm_kernel(WbArgs a, int
     for (int j = 0; j < NI; ++j) {
       const f32x4 v = acc[i][j];
       if (OUT_BF16)
-        *(u32x2 MLA_LDS*)(sb + lc * ROW + (((j * 2 + (lg >> 1)) ^ (lc & 7)) * 16) + (lg & 1) * 8) =
+        *(u32x2 MLA_LDS*)(sb + lc * ROW + (((j * 2 + (lg >> 1)) ^ (lc & SW)) * 16) + (lg & 1) * 8) =
             u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
       else
-        *(f32x4 MLA_LDS*)(sb + lc * ROW + (((j * 4 + lg) ^ (lc & 7)) * 16)) = v;
+        *(f32x4 MLA_LDS*)(sb + lc * ROW + (((j * 4 + lg) ^ (lc & SW)) * 16)) = v;
     }
 #pragma unroll
     for (int p = 0; p < 16 / RPI; ++p) {
       const int r = p * RPI + rl;
-      const u32x4 v = *(const u32x4 MLA_LDS*)(sb + r * ROW + ((cl ^ (r & 7)) * 16));
+      const u32x4 v = *(const u32x4 MLA_LDS*)(sb + r * ROW + ((cl ^ (r & SW)) * 16));
       const int64_t m = m0 + wm * (BM / 2) + i * 16 + r;
       if (m >= a.n_rows) continue;
       const int64_t at = ybase + m * a.ldy + n;
@@ -229,7 +230,7 @@ __global__ __launch_bounds__(WB_WAVES * 64, 2) void wb_gemm_kernel(WbArgs a, int
 
 // Few rows (a query block, a chunk of new tokens): the weight is read once, so what
 // counts is how much of it is in flight.  A workgroup takes 16 output channels and
-// up to 16 MB rows, and its 8 waves split K: 64-wide chunk c goes to wave c % 8,
+// up to 16 MB rows (all of them), and its 8 waves split K: 64-wide chunk c goes to wave c % 8,
 // fragments straight from memory, the next two chunks loaded ahead.  The waves'
 // sums meet in LDS and are added in wave order.
 template <bool OUT_BF16, int MB>
@@ -238,13 +239,12 @@ __global__ __launch_bounds__(512) void wb_rows_kernel(WbArgs a, int n_blocks) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lg = lane >> 4, lc = lane & 15;
   const int bt = blockIdx.x / n_blocks, n0 = (int)(blockIdx.x % n_blocks) * 16;
-  const int64_t m0 = (int64_t)blockIdx.y * 16 * MB;
   // rows past the end repeat the last one; their results are not stored
   const uint16_t* w = a.w_b + bt * a.w_batch + (int64_t)std::min(n0 + lc, a.d_out - 1) * a.ldw + lg * 8;
   const uint16_t* z[MB];
 #pragma unroll
   for (int b = 0; b < MB; ++b)
-    z[b] = a.z + bt * a.z_batch + std::min<int64_t>(m0 + b * 16 + lc, a.n_rows - 1) * a.ldz + lg * 8;
+    z[b] = a.z + bt * a.z_batch + std::min<int64_t>(b * 16 + lc, a.n_rows - 1) * a.ldz + lg * 8;
   f32x4 acc[MB];
 #pragma unroll
   for (int b = 0; b < MB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(512) void wb_rows_kernel(WbArgs a, int n_blocks) {
 #pragma unroll
       for (int b = 0; b < MB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c.w[h], c.z[h][b], acc[b], 0, 0, 0);
   };
-  constexpr int D = MB <= 2 ? 4 : 2;   // chunks in flight
+  constexpr int D = 4;   // chunks in flight
   Chunk c[D];
 #pragma unroll
   for (int d = 0; d < D; ++d) load(c[d], wave + 8 * d);
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(512) void wb_rows_kernel(WbArgs a, int n_blocks) {
     f32x4 v = part[0][b][g * 16 + r];
 #pragma unroll
     for (int k = 1; k < 8; ++k) v += part[k][b][g * 16 + r];
-    const int64_t m = m0 + b * 16 + r;
+    const int64_t m = b * 16 + r;
     if (m >= a.n_rows) continue;
     const int64_t at = bt * a.y_batch + m * a.ldy + n0 + g * 4;
 #pragma unroll
@@ -308,55 +308,60 @@ hipError_t launch_rows(const WbArgs& a, hipStream_t s) {
   const unsigned gx = (unsigned)(n_blocks * a.batch);
   if (a.n_rows <= 16)
     wb_rows_kernel<OUT_BF16, 1><<<dim3(gx), dim3(512), 0, s>>>(a, n_blocks);
-  else if (a.n_rows <= 32)
-    wb_rows_kernel<OUT_BF16, 2><<<dim3(gx), dim3(512), 0, s>>>(a, n_blocks);
   else
-    wb_rows_kernel<OUT_BF16, 4><<<dim3(gx, (unsigned)((a.n_rows + 63) / 64)), dim3(512), 0, s>>>(a, n_blocks);
+    wb_rows_kernel<OUT_BF16, 2><<<dim3(gx), dim3(512), 0, s>>>(a, n_blocks);
   return hipGetLastError();
 }
 
-template <bool OUT_BF16, int MI, int NST>
+template <bool OUT_BF16, int MI, int BN, int NST>
 hipError_t launch_tiles(const WbArgs& a, hipStream_t s) {
   const int m_tiles = (int)((a.n_rows + 32 * MI - 1) / (32 * MI));
-  const int n_tiles = (a.d_out + WB_BN - 1) / WB_BN;
+  const int n_tiles = (a.d_out + BN - 1) / BN;
   const int total = m_tiles * n_tiles * a.batch;
   // an output beyond the L2s' 32 MB cannot stay there: stored past them, it leaves
   // them to the panels (33,792 rows f32: 927 -> 882 us; 264,192 rows bf16: 6.39 -> 6.31 ms)
   const bool stream_out = a.n_rows * a.d_out * a.batch * (OUT_BF16 ? 2 : 4) > (int64_t)32 << 20;
-  wb_gemm_kernel<OUT_BF16, MI, NST><<<dim3((unsigned)(8 * ((total + 7) / 8))), dim3(WB_WAVES * 64), 0, s>>>(a, m_tiles, n_tiles, stream_out);
+  wb_gemm_kernel<OUT_BF16, MI, BN, NST><<<dim3((unsigned)(8 * ((total + 7) / 8))), dim3(WB_WAVES * 64), 0, s>>>(a, m_tiles, n_tiles, stream_out);
   return hipGetLastError();
 }
 
 template <bool OUT_BF16>
 hipError_t launch_out(const WbArgs& a, hipStream_t s) {
-  // up to 64 rows the few-row kernel (4096 -> 4096: 8.4 us at 1 row, 11.8 at 16, 16.7
-  // at 32, 23.9 at 64) against 26-28 us for the tiles; at 128 rows 43 against 28
+  // up to 32 rows the few-row kernel (4096 -> 4096: 8.4 us at 1 row, 11.8 at 16, 16.7
+  // at 32) against 17.6 us for the tiles; at 48 rows 21 against 17.6
   if (a.n_rows <= kWbFewRows && (a.d_out + 15) / 16 * (int64_t)a.batch <= INT32_MAX) return launch_rows<OUT_BF16>(a, s);
-  // Tile height: the one whose rounds of tiles over the 256 compute units cost least,
-  // a tile of 32 MI rows taken as MI + 3 (one round at K = 4096, heights 1 .. 8: 30,
-  // 34, 42, 48, 56, 63, 73, 74 us).  At 4096 channels: 2100 rows 68 us at height 5
-  // against 82 at 8, 1024 rows 40 at 2 against 76 at 8, 33,792 rows 849 at 8 against
-  // 875 at 6.
-  const int64_t n_tiles = (int64_t)((a.d_out + WB_BN - 1) / WB_BN) * a.batch;
+  // The tile whose rounds over the 256 compute units cost least.  256 channels: 32 mi
+  // rows taken as mi + 3 (here in thirds; one round at K = 4096, heights 1 .. 8: 28,
+  // 34, 42, 48, 56, 63, 73, 74 us).  While a round is not full a slice waits for its
+  // unit's direct loads, 36 KB for 32 x 256, so there are tiles of 128 channels, 20 to
+  // 32 KB (17.7, 19.6, 24.6, 25.5 us).  At 4096 channels: 128 rows 18.2 us at 32 x 128
+  // against 28 at 32 x 256, 500 rows 23 at 64 x 128 against 31, 1024 rows 35.5 at 128 x
+  // 128 against 38.6 at 64 x 256; 2100 rows 68 at 160 x 256 against 82 at height 256,
+  // 33,792 rows 849 at 256 x 256 against 875 at 192.
   int best = 8;
   int64_t cost = INT64_MAX;
-  for (int mi = 8; mi >= 1; --mi) {
-    const int64_t tiles = (a.n_rows + 32 * mi - 1) / (32 * mi) * n_tiles;
-    const int64_t c = (tiles + 255) / 256 * (mi + 3);
+  auto tile = [&](int id, int mi, int bn, int w) {
+    const int64_t tiles = (a.n_rows + 32 * mi - 1) / (32 * mi) * ((a.d_out + bn - 1) / bn) * a.batch;
+    const int64_t c = (tiles + 255) / 256 * w;
     if (c < cost) {
       cost = c;
-      best = mi;
+      best = id;
     }
-  }
+  };
+  for (int mi = 8; mi >= 2; --mi) tile(mi, mi, 256, 3 * (mi + 3));
+  for (int mi = 4; mi >= 1; --mi) tile(10 + mi, mi, 128, mi + 7);
   switch (best) {
-    case 1: return launch_tiles<OUT_BF16, 1, 4>(a, s);
-    case 2: return launch_tiles<OUT_BF16, 2, 3>(a, s);
-    case 3: return launch_tiles<OUT_BF16, 3, 3>(a, s);
-    case 4: return launch_tiles<OUT_BF16, 4, 3>(a, s);
-    case 5: return launch_tiles<OUT_BF16, 5, 3>(a, s);
-    case 6: return launch_tiles<OUT_BF16, 6, 2>(a, s);
-    case 7: return launch_tiles<OUT_BF16, 7, 2>(a, s);
-    default: return launch_tiles<OUT_BF16, 8, 2>(a, s);
+    case 2: return launch_tiles<OUT_BF16, 2, 256, 3>(a, s);
+    case 3: return launch_tiles<OUT_BF16, 3, 256, 3>(a, s);
+    case 4: return launch_tiles<OUT_BF16, 4, 256, 3>(a, s);
+    case 5: return launch_tiles<OUT_BF16, 5, 256, 3>(a, s);
+    case 6: return launch_tiles<OUT_BF16, 6, 256, 2>(a, s);
+    case 7: return launch_tiles<OUT_BF16, 7, 256, 2>(a, s);
+    case 11: return launch_tiles<OUT_BF16, 1, 128, 7>(a, s);
+    case 12: return launch_tiles<OUT_BF16, 2, 128, 6>(a, s);
+    case 13: return launch_tiles<OUT_BF16, 3, 128, 5>(a, s);
+    case 14: return launch_tiles<OUT_BF16, 4, 128, 4>(a, s);
+    default: return launch_tiles<OUT_BF16, 8, 256, 2>(a, s);
   }
 }
 

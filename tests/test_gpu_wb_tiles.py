@@ -1,5 +1,5 @@
-"""W_b at the edges of its launch rules: every tile height (picked by how the
-rows fill the compute units), the K pipelines' lengths (fewer slices than
+"""W_b at the edges of its launch rules: every tile (picked by how the rows
+fill the compute units), the K pipelines' lengths (fewer slices than
 buffers, as many, more), the few-row kernel's row blocks and its boundary with the
 tiles, and outputs whose rows are not a whole number of 16-byte chunks.  Against
 the fp64 oracle, each element also held to 3e-4 sum |w z| (+ 2^-8 |y| for bf16
@@ -14,24 +14,30 @@ from test_gpu_wb import check_wb, gpu_wb
 pytestmark = pytest.mark.gpu
 
 
-def tile_height(rows, d_out):
-    n_tiles = -(-d_out // 256)
-    cost = {mi: -(-(-(-rows // (32 * mi)) * n_tiles) // 256) * (mi + 3) for mi in range(8, 0, -1)}
+def tile(rows, d_out):
+    """(height / 32, channels) of the tile the launch rule takes."""
+    def rounds(mi, bn):
+        return -(-(-(-rows // (32 * mi)) * -(-d_out // bn)) // 256)
+    cost = {(mi, 256): rounds(mi, 256) * 3 * (mi + 3) for mi in range(8, 1, -1)}
+    cost.update({(mi, 128): rounds(mi, 128) * (mi + 7) for mi in range(4, 0, -1)})
     return min(cost, key=cost.get)
 
 
-HEIGHTS = {1: 500, 2: 1021, 3: 1535, 4: 2047, 5: 2100, 6: 3071, 7: 3577, 8: 4090}
+# tile: rows, channels
+TILES = {(1, 128): (250, 4090), (2, 128): (500, 4090), (3, 128): (767, 4090), (4, 128): (1021, 4090),
+         (2, 256): (190, 21750), (3, 256): (1535, 4090), (4, 256): (2047, 4090), (5, 256): (2100, 4090),
+         (6, 256): (3071, 4090), (7, 256): (3577, 4090), (8, 256): (4090, 4090)}
 
 
-@pytest.mark.parametrize("mi", sorted(HEIGHTS))
-@pytest.mark.parametrize("d_in,out", [(64, "f32"), (320, "bf16")])
-def test_tile_heights(mi, d_in, out):
-    n, d_out = HEIGHTS[mi], 4090
-    assert tile_height(n, d_out) == mi
-    z, w = wb_inputs(n, d_in, d_out, seed=300 + mi, z_std=1.0, w_std=d_in ** -0.5)
+@pytest.mark.parametrize("mi,bn", sorted(TILES))
+@pytest.mark.parametrize("d_in,out", [(64, "f32"), (320, "bf16"), (512, "bf16")])
+def test_tiles(mi, bn, d_in, out):
+    n, d_out = TILES[mi, bn]
+    assert tile(n, d_out) == (mi, bn)
+    z, w = wb_inputs(n, d_in, d_out, seed=300 + mi + bn, z_std=1.0, w_std=d_in ** -0.5)
     got = gpu_wb(z, w, out)
     assert np.isfinite(got).all()
-    rows = np.unique(np.concatenate([[0, 15, 16, 31, 32 * mi - 1, 32 * mi, n - 1], np.arange(0, n, 97)]))
+    rows = np.unique(np.concatenate([[0, 15, 16, 31, min(32 * mi, n) - 1, min(32 * mi, n - 1), n - 1], np.arange(0, n, 97)]))
     check_wb(got[rows], z, w, out, rows=rows)
 
 
