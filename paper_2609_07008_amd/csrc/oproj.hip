@@ -209,7 +209,9 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles) {
   // lane quantities recomputed here rather than kept live across the K loop
   const int elane = (int)__lane_id();
   float MLA_LDS* stage = (float MLA_LDS*)As + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (32 * SLD);
-  const uint16_t* zoff = (const uint16_t*)a.z_off;
+  // without z_off (every row protected) nothing is added: the lanes load from o_glob
+  const bool has_zoff = a.z_off != nullptr;
+  const uint16_t* zoff = (const uint16_t*)(has_zoff ? a.z_off : a.o_glob);
   const int prow = elane >> 3, pc4 = (elane & 7) * 4;   // read-back: row prow + 8p, channels pc4 .. +3
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
@@ -228,7 +230,7 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles) {
           const int n = n0 + wn * TN + ni * 32 + pc4;
           const int r = wm * TM + mi * 32 + p * 8 + prow;
           const int64_t orow = m0 + r < M && n < cw ? (int64_t)row_out[r] : -1;
-          const bool use = orow >= 0 && !row_flag[r];
+          const bool use = has_zoff && orow >= 0 && !row_flag[r];
           const u32x2 zz = *(const u32x2*)(zoff + (use ? orow * a.d_model + (int64_t)pg * cw + n : 0));
           addv[ni][p] = use ? zz : u32x2{0u, 0u};
         }
