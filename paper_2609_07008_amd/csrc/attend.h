@@ -7,6 +7,11 @@
 
 namespace mla {
 
+// The softmax reference of a head-row is its max over this many first keys of an item
+// (those of the item's first segment, where it is shorter).  The weight at the max is
+// exactly 1; weights above it carry bf16's rounding, so fewer keys cost accuracy.
+constexpr int kRefKeys = 64;
+
 template <int DC, int DR>
 struct Cfg {
   static constexpr int D = DC + DR;
@@ -28,6 +33,7 @@ struct Cfg {
   static constexpr int PS = BK / 16;         // 16-key contraction steps of P.V per tile
   static_assert(DR == 16 || DR % 32 == 0, "d_rope must be 16 or a multiple of 32");
   static_assert(DC % 64 == 0, "d_latent must be a multiple of 64");
+  static_assert(BK == kRefKeys, "the reference is the first tile's max");
   static_assert(kTileRows == 128, "one work item is 4 waves x 32 head-rows");
 };
 

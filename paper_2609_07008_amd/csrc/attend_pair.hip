@@ -44,6 +44,14 @@
 // loads' place in the step change the clock and the cycles together and leave the
 // time as it is.
 //
+// The reference of the softmax weights is taken before the tile loop, from the item's
+// first 64 keys as in the one-wave kernel: tiles 0 and 1 are loaded together and the
+// score waves run K Q^T over them once for the max alone.  From the first 16 keys,
+// inside the first step, it cost nothing, but rounded the weight of every larger key
+// after them (errors against 64 bits up to 5 % larger, and outputs 2^-9 of their value
+// off the one-wave kernel's; now 1e-4 and less).  The pass takes an item about 3K clk:
+// the 33K-row producer 4.59 -> 4.72 ms, the steps 1 % at most.
+//
 // Restart policy: restart.h.  A wave that sees a tile's weights sum to 2^64 or more
 // records the next step's index in restart_at (LDS atomic min); at the end of step
 // t every wave tests restart_at <= t on a value read after the step's barrier, which
@@ -75,6 +83,7 @@ struct PairCfg {
   static constexpr int QSTAGE = kTileRows / 8 * KB8;   // the item's queries at its start, in the tile layout
   static constexpr int LDS_BYTES = QSTAGE > TH_OFF + 4 * (DR / 2 * 8) ? QSTAGE : TH_OFF + 4 * (DR / 2 * 8);
   static_assert(DR == 64 && DC % 64 == 0, "rotation pairs (j, j + 32) sit in one lane of two K steps");
+  static_assert(kRefKeys == 2 * BK && NBUF >= 2, "the reference's keys are tiles 0 and 1");
   static_assert(OBS % 4 == 0 && OBV % 4 == 0, "output blocks come in whole chunk groups");
 };
 
@@ -291,7 +300,7 @@ __global__ __launch_bounds__(512, 2) void attend_pair_kernel(AttendArgs a) {
     const int abase = (lc >> 3) * C::KB8 + (lc & 7) * 128 + ((lg ^ key_swz(lc & 7)) * 16);
 
     f32x4 o[C::OBS][2];
-    float m_run[2], l_run[2], m_seen[2] = {-1e30f, -1e30f};
+    float m_run[2], l_run[2], m_seen[2];
     int lim[2], wave_lim;
     auto relocate = [&](const TileCursor& s) {
       const int ln = lane_now();
@@ -321,22 +330,49 @@ __global__ __launch_bounds__(512, 2) void attend_pair_kernel(AttendArgs a) {
     const int vbl = vbase(0), pwl = pair_p + lane * 16;
     int attempt = 0;
     TileCursor c;
+    cursor_open<C>(c, v, v.chk.first_rank);
+    relocate(c);
+    tile_barrier();   // tiles 0 and 1 have landed
+    // The reference: each head-row's max over the item's first kRefKeys keys (of its
+    // first segment).  Once per item, before the tile loop, 16 keys at a time.
+    {
+      float m[2] = {-INFINITY, -INFINITY};
+      const int n16 = c.n_keys > C::BK ? kRefKeys / 16 : C::BK / 16;
+#pragma unroll 1
+      for (int b = 0; b < n16; ++b) {
+        const int at = abase + (b >> 1) * C::TILE_BYTES + (b & 1) * 2 * C::KB8;
+        f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+        bf16x8 ka[4];
+        auto kfrag = [&](int ks) -> bf16x8 { return *(const bf16x8 MLA_LDS*)(L + (at ^ ((ks & 1) * 64)) + (ks >> 1) * 1024); };
+#pragma unroll
+        for (int j = 0; j < 3; ++j) ka[j] = kfrag(j);
+#pragma unroll
+        for (int ks = 0; ks < C::KS; ++ks) {
+          if (ks + 3 < C::KS) ka[(ks + 3) % 4] = kfrag(ks + 3);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb) s[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[ks % 4], qf[ks][rb], s[rb], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        const int k0 = b * 16 + (lane_now() >> 4) * 4;
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) m[rb] = fmaxf(m[rb], i > lim[rb] - k0 ? -INFINITY : s[rb][i]);
+      }
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        m_run[rb] = quad_max(m[rb]) * sl2;
+        m_seen[rb] = fmaxf(-1e30f, m_run[rb]);
+      }
+    }
     for (;;) {
 #pragma unroll
       for (int d = 0; d < C::OBS; ++d)
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) o[d][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb) {
-        m_run[rb] = m_seen[rb];
-        l_run[rb] = 0.f;
-      }
+      l_run[0] = l_run[1] = 0.f;
       const bool may_vote = restart_allowed(attempt);
-      bool first_tile = attempt == 0;
-      int first = v.chk.first_rank;
-      asm volatile("" : "+s"(first));   // opened anew by each attempt, not held across the loop
-      cursor_open<C>(c, v, first);
-      relocate(c);
       bf16x8 pf[2] = {bf16x8{}, bf16x8{}};
       bf16x8 vt[C::OBS];
 #pragma unroll
@@ -423,20 +459,7 @@ __global__ __launch_bounds__(512, 2) void attend_pair_kernel(AttendArgs a) {
               if (i > rel) s[kb][rb][i] = -INFINITY;
           }
         };
-        if (__builtin_expect((tk0 + C::BK - 1 > wave_lim) | first_tile, 0)) {
-          mask(0);
-          if (first_tile) {   // the reference: each head-row's max over the item's first 16 keys
-#pragma unroll
-            for (int rb = 0; rb < 2; ++rb) {
-              float m = s[0][rb][0];
-#pragma unroll
-              for (int i = 1; i < 4; ++i) m = fmaxf(m, s[0][rb][i]);
-              m_run[rb] = quad_max(m) * sl2;
-              m_seen[rb] = fmaxf(m_seen[rb], m_run[rb]);
-            }
-            first_tile = false;
-          }
-        }
+        if (__builtin_expect(tk0 + C::BK - 1 > wave_lim, 0)) mask(0);
         // The second 16 keys' scores; between their MFMAs the first 16 keys' weights
         // and the reads of this wave's V^T fragments.
         const int vb = vbl + cur;
@@ -480,6 +503,13 @@ __global__ __launch_bounds__(512, 2) void attend_pair_kernel(AttendArgs a) {
       tile_barrier();
       if (tid == 0) restart_at = ~0u;
       ++attempt;
+      m_run[0] = m_seen[0];
+      m_run[1] = m_seen[1];
+      int first = v.chk.first_rank;
+      asm volatile("" : "+s"(first));   // opened anew, not held across the loop
+      cursor_open<C>(c, v, first);
+      relocate(c);
+      tile_barrier();   // tiles 0 and 1 have landed
     }
     float inv[2];
 #pragma unroll
@@ -517,17 +547,18 @@ __global__ __launch_bounds__(512, 2) void attend_pair_kernel(AttendArgs a) {
       asm volatile("" : "+s"(first));   // opened anew by each attempt, not held across the loop
       cursor_open<C>(c, v, first);
       issue_block<C>(a.kv, c, L, pair);
+      bool have = cursor_next<C>(c, v) != 0;   // tile t (from 1) exists
+      if (have) issue_block<C>(a.kv, c, L + C::TILE_BYTES, pair);
 #pragma unroll
       for (int d = 0; d < C::OBV; ++d)
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) o[d][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
       bool restart = false;
-      tile_barrier();                      // step 0: tile 0 has landed
+      tile_barrier();                      // tiles 0 and 1 have landed
+      tile_barrier();                      // step 0
       unsigned t = 1;
       int cur = 0;                         // buffer of tile t - 1
       int pcur = 0;                        // weight buffer of tile t - 1
-      bool have = cursor_next<C>(c, v) != 0;   // tile t exists
-      if (have) issue_block<C>(a.kv, c, L + C::TILE_BYTES, pair);
       for (;;) {
         tile_barrier();                    // step t: tile t has landed, the weights of tile t - 1 are written
         const unsigned vote = *(volatile unsigned MLA_LDS*)&restart_at;

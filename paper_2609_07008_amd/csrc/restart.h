@@ -2,16 +2,17 @@
 // stable log-sum-exp of SegmentedLSEMerge).
 //
 // The tile loop scales every weight against a fixed reference max m_run (log2
-// units), set from an item's first tile, so a later tile's weights 2^(s - m_run)
-// are not bounded by 1.  A lane whose weights in one tile sum to 2^64 or more
+// units), set from an item's first 64 keys, so a later key's weight 2^(s - m_run)
+// is not bounded by 1.  A lane whose weights in one tile sum to 2^64 or more
 // (finite or +inf) votes to restart the work item with a raised reference; fp32
 // sums and bf16 weights below 2^64 hold every weight without loss.  The rules
 // below are shared by the kernel and a CPU test:
 //   - only a sum >= 2^64 votes; NaN never does (a NaN score, key or query makes
 //     its head-row NaN, which no reference can repair);
 //   - the raise is log2 of the sum (at least 64), or 128 when a weight or the
-//     sum overflowed fp32; a head-row whose two lanes cast no vote keeps its
-//     reference, so a restart recomputes it bit for bit;
+//     sum overflowed fp32; a head-row none of whose lanes (two in the one-wave
+//     kernel, four in the two-wave one) casts a vote keeps its reference, so a
+//     restart recomputes it bit for bit;
 //   - an item makes at most kMaxAttempts passes: the last one casts no vote, so
 //     the loop ends even when a raise cannot help (an infinite score, or a
 //     reference so large that adding 128 does not change it).  Weights that
@@ -48,7 +49,7 @@ __host__ __device__ inline float restart_raise(float rsum) {
 __host__ __device__ inline bool restart_allowed(int attempt) { return attempt + 1 < kMaxAttempts; }
 
 // reference of a head-row for the next pass: the largest of what it has seen so
-// far and its current reference plus the larger raise of its two lane halves
+// far and its current reference plus the larger of two raises (its lanes' largest)
 __host__ __device__ inline float raised_reference(float m_seen, float m_run, float raise_a, float raise_b) {
   return fmaxf(m_seen, m_run + fmaxf(raise_a, raise_b));
 }
