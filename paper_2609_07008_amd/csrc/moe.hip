@@ -14,18 +14,24 @@
 // experts a lane at a time while the row before is ranked.  Keys are 32-bit here:
 // the low 8 bits of the weight's code give way to the index.  Each lane keeps its
 // four largest keys sorted (a max and three medians per key); a round takes the
-// row's maximum of the lanes' largest (four DPP steps) and the owner drops it.  Two
-// cases need the exact ranking: neighbours in rank whose codes differ in the low 8
-// bits only, or a lane whose four keys are all taken; a wave that sees one ranks
-// its four rows over with 64-bit keys (rank_exact).  For softmax weights that is
-// about one wave in fifty.
+// row's maximum of the lanes' largest (four DPP steps) and the owner drops it.  The
+// weights are then fetched, and the list is right if they stand in order and top_k - 1
+// experts come before the last.  The order is compared in every row (equal weights are
+// in order: the lower expert first).  The count, a second read of the row, only in waves
+// with a row where something could belong inside: a runner-up that shares the upper
+// bits of the last rank's code, or a lane whose four keys are all taken; one wave in
+// seventy on softmax weights, one in four where the logits were bf16 and weights repeat.
+// A wave that finds a wrong list ranks its rows over with 64-bit keys (rank_exact): one
+// in a thousand, weights that differ in the low 8 bits of their codes only.
 // Above 256 experts a whole wave holds a row and every round is exact.
 //
-// What bounds it is vector issue: 64-bit rounds over all of a lane's experts took 280
-// wave instructions a row, these about 110.  264,192 rows x 256 experts 136 -> 86 us
-// (3.3 TB/s), x 128 86 -> 59, x 64 68 -> 49, x 16 53 -> 37; four waves a SIMD (at
-// most 128 registers): with fewer registers the exact ranking spills (110 us), with
-// more too few waves hide the loads (90).
+// What bounds it is vector issue: 64-bit rounds over all of a lane's experts took 278
+// wave instructions a row, these 115, 134 with repeated weights.  264,192 rows x 256
+// experts 127 -> 73 us (4.0 TB/s; bf16 logits 127 -> 84, all weights equal 127 -> 102),
+// x 128 83 -> 51, x 64 68 -> 45, x 16 52 -> 33.  Any two neighbours with like upper bits,
+// equal weights too, sent to the exact ranking took bf16 logits 160 us.  Four waves a
+// SIMD (at most 128 registers): with fewer registers the exact ranking spills (110 us),
+// with more too few waves hide the loads (90).
 // A second kernel over a few blocks counts the rows that execute each expert
 // (per-block LDS histograms added into expert_count, which the first one clears).
 #include "moe.h"
@@ -205,6 +211,12 @@ __device__ __forceinline__ uint32_t row_max_u32(uint32_t v) {
   v = max_u32(v, dpp<0x141>(v));
   return max_u32(v, dpp<0x140>(v));
 }
+__device__ __forceinline__ uint32_t row_sum_u32(uint32_t v) {
+  v += dpp<0xB1>(v);
+  v += dpp<0x4E>(v);
+  v += dpp<0x141>(v);
+  return v + dpp<0x140>(v);
+}
 // lane J of each row of 16, in every lane of the row (row_newbcast)
 template <int J>
 __device__ __forceinline__ float row_bcast(float v) {
@@ -268,41 +280,62 @@ __global__ __launch_bounds__(256, 4) void moe_fanout_kernel(MoeArgs a) {
       load_row16<NV, VEC>(a, rn < last ? rn : last, sl, cur);
     }
     int32_t my_id = 0;
-    uint32_t before = 0xFFFFFFFFu;
-    bool unsure = false;
+    uint32_t last_key = 0;   // of rank top_k
 #pragma unroll
-    for (int j = 0; j <= kMoeMaxTopK; ++j) {
-      if (j <= TK) {
+    for (int j = 0; j < kMoeMaxTopK; ++j) {
+      if (j < TK) {
         const uint32_t M = row_max_u32(m[0]);
-        // code bits alike in neighbouring ranks, or nothing left to take
-        unsure |= (M >> 8) == (before >> 8) || (j < TK && (M >> 8) == 0);
-        before = M;
-        if (j < TK) {
-          if (sl == j) my_id = 255 - (int32_t)(M & 0xFFu);
-          const bool own = m[0] == M;
+        last_key = M;
+        if (sl == j) my_id = 255 - (int32_t)(M & 0xFFu);
+        const bool own = m[0] == M;
 #pragma unroll
-          for (int d = 0; d + 1 < DEPTH; ++d) m[d] = own ? m[d + 1] : m[d];
-          m[DEPTH - 1] = own ? 0u : m[DEPTH - 1];
-          if (NV > DEPTH) unsure |= m[0] == 0;   // this lane's fifth key is not known
-        }
+        for (int d = 0; d + 1 < DEPTH; ++d) m[d] = own ? m[d + 1] : m[d];
+        m[DEPTH - 1] = own ? 0u : m[DEPTH - 1];
       }
     }
-    float my_w;
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(unsure) != 0, 0)) {
-      float row[NV];
-      load_row<16, NV>(a, rc, sl, row);
-      int32_t id[kMoeMaxTopK];
-      float w[kMoeMaxTopK];
-      rank_exact<16, NV>(a, row, sl, id, w);
-      my_w = 0.0f;
+    float my_w = a.router[rc * E + my_id];   // lanes past top_k: expert 0, not used
+    // The key order is the weights' unless two weights whose codes share their upper 24
+    // bits stand the wrong way round.  Inside the ranked list neighbours show that.
+    const uint32_t code = total_order_bits(my_w);
+    const uint32_t prev = dpp<0x111>(code);   // row_shr:1: the rank before
+    bool wrong = sl > 0 && sl < TK && prev < code;
+    // Past it only a runner-up with the last rank's upper bits, or the unknown fifth key
+    // of a lane that gave its four, could belong inside.
+    const bool open = (row_max_u32(m[0]) >> 8) == (last_key >> 8) || (NV > DEPTH && m[0] == 0);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(wrong || open) != 0, 0)) {
+      int ln = sl;
+      asm volatile("" : "+v"(ln));   // the addresses below are formed here, not held across the rows
+      {
+        // a ranked list in order is right if top_k - 1 experts come before its last
+        const int end = (lane & 48) + TK - 1;
+        const uint32_t end_code = (uint32_t)__shfl((int)code, end, 64);
+        const int end_id = __shfl(my_id, end, 64);
+        float row[NV];
+        load_row<16, NV>(a, rc, ln, row);
+        uint32_t before = 0;
 #pragma unroll
-      for (int j = 0; j < kMoeMaxTopK; ++j)
-        if (sl == j) {
-          my_id = id[j];
-          my_w = w[j];
+        for (int i = 0; i < NV; ++i) {
+          const uint32_t c = total_order_bits(row[i]);
+          const int e = 16 * i + ln;
+          before += e < E && (c > end_code || (c == end_code && e < end_id));
         }
-    } else {
-      my_w = a.router[rc * E + my_id];   // lanes past top_k: expert 0, not used
+        wrong |= row_sum_u32(before) != (uint32_t)(TK - 1);
+      }
+      if (__builtin_amdgcn_ballot_w64(wrong) != 0) {
+        asm volatile("" : "+v"(ln));   // and the row is read again, not kept until here
+        float row[NV];
+        load_row<16, NV>(a, rc, ln, row);
+        int32_t id[kMoeMaxTopK];
+        float w[kMoeMaxTopK];
+        rank_exact<16, NV>(a, row, ln, id, w);
+        my_w = 0.0f;
+#pragma unroll
+        for (int j = 0; j < kMoeMaxTopK; ++j)
+          if (sl == j) {
+            my_id = id[j];
+            my_w = w[j];
+          }
+      }
     }
     // fanout, decided in float32 in rank order: lane j of the row holds rank j
     float S = row_bcast<0>(my_w);
