@@ -473,7 +473,8 @@ mla_status mla_moe_fanout(int64_t n_rows, int32_t n_experts, const float* router
 /* ----------------------------------------------------------------------------
  * mla_shared_wb -- the shared second output projection y = W_b z that every row's
  * group-sliced state z meets after the artifact add (Sec. 2.1 eq:factorization,
- * Alg. 2 returns W_b z).  bf16 MFMA with fp32 accumulation.
+ * Alg. 2 returns W_b z).  bf16 MFMA with fp32 accumulation, in an order that does
+ * not depend on n_rows: a row of z gives the same bits in any call.
  *
  *   n_rows, d_in, d_out  N rows; z width (a multiple of 64, at most 16384);
  *                  output channels (>= 1).

@@ -19,7 +19,10 @@
 // 2 or 16 7-14 %).
 //
 // 264,192 rows, 4096 -> 4096: bf16 y 7.10 -> 6.37 ms (1.39 PFLOP/s), f32 y 7.40 ->
-// 6.86; 2100 rows f32 81 -> 66 us, 300 rows 76 -> 21, 16 rows 72 -> 12.
+// 6.86; 2100 rows f32 81 -> 66 us, 300 rows 76 -> 21, 16 rows 72 -> 8.
+//
+// Every tile and the few-row kernel add an element's products in the same order: a row of
+// y does not depend on how many rows the call has.
 #include "wb.h"
 
 #include <algorithm>
@@ -31,7 +34,7 @@ namespace {
 constexpr int WB_BK = 64;
 constexpr int WB_WAVES = 8;                           // 2 x 4 waves of (BM/2) x (BN/4)
 constexpr int WB_ROWB = WB_BK * 2;                    // bytes of one row of a slice
-constexpr int64_t kWbFewRows = 32;
+constexpr int64_t kWbFewRows = 32, kWbFewBlocks = 512;   // largest requests of the few-row kernel
 constexpr int WB_GM = 8;                              // row panels per column panel in the tile walk
 
 __device__ __forceinline__ void wb_dma16(const void* base, uint32_t voff, const unsigned char MLA_LDS* dst) {
@@ -229,76 +232,84 @@ __global__ __launch_bounds__(WB_WAVES * 64, 2) void wb_gemm_kernel(WbArgs a, int
 }
 
 // Few rows (a query block, a chunk of new tokens): the weight is read once, so what
-// counts is how much of it is in flight.  A workgroup takes 16 output channels and
-// up to 16 MB rows (all of them), and its 8 waves split K: 64-wide chunk c goes to wave c % 8,
-// fragments straight from memory, the next two chunks loaded ahead.  The waves'
-// sums meet in LDS and are added in wave order.
-template <bool OUT_BF16, int MB>
-__global__ __launch_bounds__(512) void wb_rows_kernel(WbArgs a, int n_blocks) {
-  __shared__ f32x4 part[8][MB][64];
+// counts is how much of it is in flight.  A workgroup takes 16 output channels and up
+// to 16 MB rows (all of them); its 8 waves bring 512 of K at a time, a kilobyte of one
+// weight or z row a direct load, into NST stages (128 KB at 16 rows, 144 KB at 32) and
+// wave b < MB runs the MFMAs of row block b, one after the other over K: the sum of an
+// element has the order it has in the tiles, so a row of y has the same bits whatever
+// the number of rows.  Chunk c of row r sits at c ^ (r & 15).
+// 4096 -> 4096: 7.7 us at 1 row, 7.4 at 16, 9.1 at 32 (K split over the waves, fragments
+// straight from memory: 8.2, 11.4, 16.3); 16384 -> 4096 28, 29, 33 us (27, 35, 48).
+template <bool OUT_BF16, int MB, int NST>
+__global__ __launch_bounds__(WB_WAVES * 64) void wb_rows_kernel(WbArgs a, int n_blocks) {
+  constexpr int BK = 512, ROWB = BK * 2, ROWS = 16 + 16 * MB, STAGE = ROWS * ROWB;
+  constexpr int LPW = ROWS / WB_WAVES;           // 1 KB direct loads per wave and stage
+  static_assert(ROWB == 1024 && ROWS % WB_WAVES == 0, "a load takes a row");
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lg = lane >> 4, lc = lane & 15;
   const int bt = blockIdx.x / n_blocks, n0 = (int)(blockIdx.x % n_blocks) * 16;
   // rows past the end repeat the last one; their results are not stored
-  const uint16_t* w = a.w_b + bt * a.w_batch + (int64_t)std::min(n0 + lc, a.d_out - 1) * a.ldw + lg * 8;
-  const uint16_t* z[MB];
+  const unsigned char* src[LPW];
 #pragma unroll
-  for (int b = 0; b < MB; ++b)
-    z[b] = a.z + bt * a.z_batch + std::min<int64_t>(b * 16 + lc, a.n_rows - 1) * a.ldz + lg * 8;
-  f32x4 acc[MB];
-#pragma unroll
-  for (int b = 0; b < MB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int nc = a.d_in / WB_BK;
-  struct Chunk {
-    bf16x8 w[2], z[2][MB];
-  };
-  auto load = [&](Chunk& c, int ch) {
-    const int k = std::min(ch, nc - 1) * WB_BK;   // past the end: the last chunk again, not used
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      c.w[h] = *(const bf16x8*)(w + k + h * 32);
-#pragma unroll
-      for (int b = 0; b < MB; ++b) c.z[h][b] = *(const bf16x8*)(z[b] + k + h * 32);
-    }
-  };
-  auto mul = [&](const Chunk& c) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int b = 0; b < MB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c.w[h], c.z[h][b], acc[b], 0, 0, 0);
-  };
-  constexpr int D = 4;   // chunks in flight
-  Chunk c[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) load(c[d], wave + 8 * d);
-  for (int ch = wave; ch < nc; ch += 8 * D) {
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      if (ch + 8 * d < nc) mul(c[d]);
-      load(c[d], ch + 8 * (d + D));
-    }
+  for (int j = 0; j < LPW; ++j) {
+    const int r = wave * LPW + j;
+    src[j] = (const unsigned char*)(r < 16 ? a.w_b + bt * a.w_batch + (int64_t)std::min(n0 + r, a.d_out - 1) * a.ldw
+                                           : a.z + bt * a.z_batch + std::min<int64_t>(r - 16, a.n_rows - 1) * a.ldz);
   }
+  auto load = [&](int s, int st) {   // past the end of K: the last chunk again, not used
 #pragma unroll
-  for (int b = 0; b < MB; ++b) part[wave][b][lane] = acc[b];
-  __syncthreads();
-  // lane lg*16 + lc of block b holds row b*16 + lc, channels lg*4 .. +3; thread t sums
-  // four channels of one row, the four lane groups of a row in neighbouring threads
-  for (int i = tid; i < MB * 64; i += 512) {
-    const int b = i >> 6, r = (i & 63) >> 2, g = i & 3;
-    f32x4 v = part[0][b][g * 16 + r];
-#pragma unroll
-    for (int k = 1; k < 8; ++k) v += part[k][b][g * 16 + r];
-    const int64_t m = b * 16 + r;
-    if (m >= a.n_rows) continue;
-    const int64_t at = bt * a.y_batch + m * a.ldy + n0 + g * 4;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (n0 + g * 4 + e >= a.d_out) continue;
-      if (OUT_BF16)
-        ((__bf16*)a.y)[at + e] = (__bf16)v[e];
-      else
-        ((float*)a.y)[at + e] = v[e];
+    for (int j = 0; j < LPW; ++j) {
+      const int r = wave * LPW + j;
+      const uint32_t at = std::min((uint32_t)(s * ROWB + (lane ^ (r & 15)) * 16), (uint32_t)(a.d_in * 2 - 16));
+      wb_dma16(src[j], at, (const unsigned char MLA_LDS*)(lds + st + r * ROWB));
     }
+  };
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  const unsigned char MLA_LDS* L = (const unsigned char MLA_LDS*)lds;
+  const int nk = a.d_in / 32, ns = (a.d_in + BK - 1) / BK;
+#pragma unroll
+  for (int p = 0; p < NST - 1; ++p) load(p, p * STAGE);
+  int st = 0;
+  for (int s = 0; s < ns; ++s) {
+    // stage s has landed, and every wave has read stage s - 1, whose buffer is next
+    wb_barrier<(NST - 2) * LPW>();
+    load(s + NST - 1, st == 0 ? (NST - 1) * STAGE : st - STAGE);
+    if (wave < MB) {
+      const unsigned char MLA_LDS* pw = L + st + lc * ROWB;
+      const unsigned char MLA_LDS* pz = L + st + (16 + wave * 16 + lc) * ROWB;
+      const int left = nk - s * (BK / 32);
+      constexpr int N = BK / 32, AHEAD = 4;   // fragments read ahead of their MFMA
+      bf16x8 fw[N], fz[N];
+      auto frag = [&](int k) {
+        const int o = ((k * 4 + lg) ^ lc) * 16;
+        fw[k] = *(const bf16x8 MLA_LDS*)(pw + o);
+        fz[k] = *(const bf16x8 MLA_LDS*)(pz + o);
+      };
+#pragma unroll
+      for (int k = 0; k < AHEAD; ++k) frag(k);
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        if (k + AHEAD < N) frag(k + AHEAD);
+        __builtin_amdgcn_sched_barrier(0);
+        if (k < left) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[k], fz[k], acc, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    st = st == (NST - 1) * STAGE ? 0 : st + STAGE;
+  }
+  wb_barrier<0>();   // the loads past the end have landed
+  if (wave >= MB) return;
+  const int64_t m = wave * 16 + lc;
+  if (m >= a.n_rows) return;
+  const int64_t at = bt * a.y_batch + m * a.ldy + n0 + lg * 4;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (n0 + lg * 4 + e >= a.d_out) continue;
+    if (OUT_BF16)
+      ((__bf16*)a.y)[at + e] = (__bf16)acc[e];
+    else
+      ((float*)a.y)[at + e] = acc[e];
   }
 }
 
@@ -307,9 +318,9 @@ hipError_t launch_rows(const WbArgs& a, hipStream_t s) {
   const int n_blocks = (a.d_out + 15) / 16;
   const unsigned gx = (unsigned)(n_blocks * a.batch);
   if (a.n_rows <= 16)
-    wb_rows_kernel<OUT_BF16, 1><<<dim3(gx), dim3(512), 0, s>>>(a, n_blocks);
+    wb_rows_kernel<OUT_BF16, 1, 4><<<dim3(gx), dim3(WB_WAVES * 64), 0, s>>>(a, n_blocks);
   else
-    wb_rows_kernel<OUT_BF16, 2><<<dim3(gx), dim3(512), 0, s>>>(a, n_blocks);
+    wb_rows_kernel<OUT_BF16, 2, 3><<<dim3(gx), dim3(WB_WAVES * 64), 0, s>>>(a, n_blocks);
   return hipGetLastError();
 }
 
@@ -327,9 +338,13 @@ hipError_t launch_tiles(const WbArgs& a, hipStream_t s) {
 
 template <bool OUT_BF16>
 hipError_t launch_out(const WbArgs& a, hipStream_t s) {
-  // up to 32 rows the few-row kernel (4096 -> 4096: 8.4 us at 1 row, 11.8 at 16, 16.7
-  // at 32) against 17.6 us for the tiles; at 48 rows 21 against 17.6
-  if (a.n_rows <= kWbFewRows && (a.d_out + 15) / 16 * (int64_t)a.batch <= INT32_MAX) return launch_rows<OUT_BF16>(a, s);
+  // Up to 32 rows and 512 workgroups of 16 channels, two rounds over the compute units,
+  // the few-row kernel: 4096 -> 4096 7.8 us at 1 row, 8.9 at 32 (tiles 16.4, 17.3), -> 8192
+  // 15.3, 18.5 (17.2, 17.6), 1024 -> 8192 7.6, 7.7 (7.9, 8.3).  Wider outputs fill the chip
+  // with tiles, which read z once for 128 channels: 4096 -> 12288 17.9, 19.0 us against
+  // 22.0, 27.0, -> 32768 42.8, 43.8 against 51.5, 63.7.
+  const int64_t few_blocks = ((int64_t)a.d_out + 15) / 16 * a.batch;
+  if (a.n_rows <= kWbFewRows && few_blocks <= kWbFewBlocks) return launch_rows<OUT_BF16>(a, s);
   // The tile whose rounds over the 256 compute units cost least.  256 channels: 32 mi
   // rows taken as mi + 3 (here in thirds; one round at K = 4096, heights 1 .. 8: 28,
   // 34, 42, 48, 56, 63, 73, 74 us).  While a round is not full a slice waits for its

@@ -46,3 +46,23 @@ def test_tiles(mi, bn, d_in, out):
 def test_few_rows(n, d_in, d_out, out):
     z, w = wb_inputs(n, d_in, d_out, seed=500 + n, z_std=1.0, w_std=d_in ** -0.5)
     check_wb(gpu_wb(z, w, out), z, w, out)
+
+
+@pytest.mark.parametrize("d_in,d_out,out", [(64, 16, "f32"), (448, 37, "bf16"), (576, 1024, "f32"), (1600, 130, "f32"), (4160, 19, "bf16"),
+                                            (128, 8192, "bf16"), (128, 8193, "f32")])
+def test_a_row_does_not_depend_on_the_number_of_rows(d_in, d_out, out):
+    """Every launch rule adds an element's products in the same order: the first rows
+    of any request have the bits they have in a larger one."""
+    import torch
+    from paper_2609_07008_amd import mla
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d_in)
+    z = torch.empty((2100, d_in), device="cuda").normal_(0, 1, generator=gen).bfloat16()
+    w = torch.empty((d_out, d_in), device="cuda").normal_(0, d_in ** -0.5, generator=gen).bfloat16()
+    dtype = torch.bfloat16 if out == "bf16" else torch.float32
+    whole = torch.empty((2100, d_out), dtype=dtype, device="cuda")
+    mla.shared_wb(z, w, whole)
+    for n in (1, 7, 16, 17, 32, 33, 65, 300, 700, 1100):
+        y = torch.full((n, d_out), float("nan"), dtype=dtype, device="cuda")
+        mla.shared_wb(z[:n].contiguous(), w, y)
+        assert torch.equal(y, whole[:n]), n
