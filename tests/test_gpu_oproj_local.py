@@ -1,12 +1,11 @@
 """The o-proj's Local pass at each of its tiles (64, 128, 256 rows of 256 channels, 32
-and 64 rows of 128: picked by how the protected rows fill the compute units) and
-around their edges, with
-projection groups of 512, 448 and 96 channels (whole, ragged and part column
-tiles), dense and sliced, head widths of 64, 512 and 576, f32 and bf16 z, and a
-device count below the capacity.  Reference: z_online of eq:offonline in float64
-from the same bf16 values.  Bound per element: 3e-4 sum |o w| for the f32
-accumulation, 2^-8 of the partial sums for a bf16 z (it is rounded after each
-pass)."""
+and 64 rows of 128: picked by how the protected rows fill the compute units, asserted
+for each case) and around their edges, with more tiles than workgroups, projection
+groups of 1024, 512, 448, 128 and 96 channels (whole, ragged and part column tiles),
+dense and sliced, head widths of 64, 512 and 576, f32 and bf16 z, and a device count
+below the capacity.  Reference: z_online of eq:offonline in float64 from the same bf16
+values.  Bound per element: 3e-4 sum |o w| for the f32 accumulation, 2^-8 of the
+partial sums for a bf16 z (it is rounded after each pass)."""
 from types import SimpleNamespace
 
 import numpy as np
@@ -20,19 +19,33 @@ def geom(H, G, d_c, d_r, d_model, n_pg, rotary=False):
                            softmax_scale=1.0, rope_base=10000.0, value_rope=rotary)
 
 
-# geometry, rows, protected rows
+def tile(g, p):
+    """(rows, channels, rounds over the 256 workgroups) of the tile the device rule takes for p protected rows."""
+    cw = g.d_model // g.n_proj_groups
+    rounds = {(bm, bn): -(-(-(-p // bm) * -(-cw // bn) * g.n_proj_groups) // 256) for bm, bn in WEIGHT}
+    bm, bn = min(WEIGHT, key=lambda t: rounds[t] * WEIGHT[t])
+    return bm, bn, rounds[bm, bn]
+
+
+WEIGHT = {(256, 256): 33, (128, 256): 21, (64, 256): 15, (64, 128): 9, (32, 128): 8}   # cost of a round, in the rule's order
+
+# geometry, rows, protected rows; the tile and its rounds over the workgroups
 CASES = {
-    "height32_one_row": (geom(64, 8, 512, 64, 4096, 8), 300, 1),
-    "height32": (geom(64, 8, 512, 64, 4096, 8), 300, 255),
-    "height64_narrow": (geom(64, 8, 512, 64, 4096, 8), 700, 511),
-    "height64_narrow_edge": (geom(64, 8, 512, 64, 4096, 8), 700, 257),
-    "height64": (geom(64, 8, 512, 64, 4096, 8), 1100, 1023),
-    "height128": (geom(64, 8, 512, 64, 4096, 8), 2100, 1030),
-    "height256": (geom(64, 8, 512, 64, 4096, 8), 2500, 2400),
-    "ragged_columns": (geom(32, 4, 512, 64, 4 * 448, 4), 400, 333),
-    "narrow_groups": (geom(12, 4, 64, 16, 4 * 96, 4), 500, 97),
-    "dense": (geom(16, 2, 512, 64, 1024, 1), 260, 70),
-    "rotary": (geom(16, 2, 512, 64, 512, 2, rotary=True), 200, 65),
+    "height32_one_row": (geom(64, 8, 512, 64, 4096, 8), 300, 1, (32, 128, 1)),
+    "height32": (geom(64, 8, 512, 64, 4096, 8), 300, 255, (32, 128, 1)),
+    "height64_narrow": (geom(64, 8, 512, 64, 4096, 8), 700, 511, (64, 128, 1)),
+    "height64_narrow_edge": (geom(64, 8, 512, 64, 4096, 8), 700, 257, (64, 128, 1)),
+    "height64": (geom(64, 8, 512, 64, 4096, 8), 1100, 1023, (64, 256, 1)),
+    "height128": (geom(64, 8, 512, 64, 4096, 8), 2100, 1030, (128, 256, 1)),
+    "height256": (geom(64, 8, 512, 64, 4096, 8), 2500, 2400, (256, 256, 1)),
+    "ragged_columns": (geom(32, 4, 512, 64, 4 * 448, 4), 400, 333, (32, 128, 1)),
+    "narrow_groups": (geom(12, 4, 64, 16, 4 * 96, 4), 500, 97, (32, 128, 1)),
+    "dense": (geom(16, 2, 512, 64, 1024, 1), 260, 70, (32, 128, 1)),
+    "rotary": (geom(16, 2, 512, 64, 512, 2, rotary=True), 200, 65, (32, 128, 1)),
+    # more tiles than workgroups: a workgroup walks several
+    "height128_three_rounds": (geom(64, 8, 512, 64, 4096, 8), 4300, 4203, (128, 256, 3)),
+    "height64_narrow_two_rounds": (geom(8, 1, 64, 16, 128, 1), 17000, 16501, (64, 128, 2)),
+    "height256_three_rounds": (geom(16, 4, 64, 16, 8 * 512, 4), 11000, 10800, (256, 256, 3)),
 }
 
 
@@ -41,7 +54,8 @@ CASES = {
 def test_local_pass(name, z_dtype):
     import torch
     from paper_2609_07008_amd import mla
-    g, n, p = CASES[name]
+    g, n, p, shape = CASES[name]
+    assert tile(g, p) == shape
     hpg, dv, cw = g.n_heads // g.n_groups, mla.head_width(g), g.d_model // g.n_proj_groups
     gen = torch.Generator(device="cuda")
     gen.manual_seed(11 * n + p)
@@ -90,7 +104,7 @@ def test_no_artifact_when_every_row_is_protected(name):
     not read for a protected row."""
     import torch
     from paper_2609_07008_amd import mla
-    g, n, _ = CASES[name]
+    g, n = CASES[name][:2]
     hpg, dv, cw = g.n_heads // g.n_groups, mla.head_width(g), g.d_model // g.n_proj_groups
     gen = torch.Generator(device="cuda")
     gen.manual_seed(n)
