@@ -55,17 +55,18 @@ def device_asm(tmp_path_factory):
         return dict(ex.map(compile_one, SOURCES))
 
 
-def _direct_load_sources():
-    return sorted(f for f in os.listdir(CSRC)
-                  if f.endswith(".hip") and "global_load_lds_dwordx4" in open(os.path.join(CSRC, f)).read())
+def _direct_load_sources(device_asm):
+    """sources whose code holds an asm statement that sets m0 or issues a direct load"""
+    return sorted(src for src, lines in device_asm.items()
+                  if any(a and (c.startswith("global_load_lds") or re.search(r"\bm0\b", c)) for c, a in lines))
 
 
-def test_direct_load_sources_found():
-    assert {"attend.hip", "wb.hip"} <= set(_direct_load_sources())
+def test_direct_load_sources_found(device_asm):
+    assert {"attend.hip", "attend_pair.hip", "oproj.hip", "wb.hip"} <= set(_direct_load_sources(device_asm))
 
 
 def test_compiler_keeps_nothing_in_m0(device_asm):
-    for src in _direct_load_sources():
+    for src in _direct_load_sources(device_asm):
         outside = [c for c, a in device_asm[src] if not a and re.search(r"\bm0\b", c)]
         assert not outside, (src, outside[:10])
 
