@@ -41,23 +41,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ int rotl3(int k) { return ((k << 1) | (k >> 2)) & 7; }
 
-// 16-byte direct global->LDS load: lane i writes LDS bytes [dst + 16 i, +16) of
-// the wave-uniform destination `dst`.  Issued through inline asm so that the
-// compiler's wait-count pass does not treat every later LDS read as a possible
-// alias (it would wait for the prefetch of the next tile); the tile loop waits
-// for these loads explicitly (s_waitcnt vmcnt + barrier).
-__device__ __forceinline__ void dma16(const void* base, uint32_t voff, const unsigned char MLA_LDS* dst) {
-  const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)dst);
-  // the base is wave-uniform; make that explicit so it is held in scalar registers.
-  // readfirstlane returns a signed int: zero-extend each half through uint32_t.
-  const uint64_t b = (uint64_t)(uintptr_t)base;
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-  const uint64_t bs = ((uint64_t)hi << 32) | (uint64_t)lo;
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(voff), "s"(bs), "s"(m0) : "memory", "m0");
-}
-
 __device__ __forceinline__ int wave_min_i(int v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {

@@ -194,6 +194,30 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
+// 16-byte direct global->LDS load: lane i writes LDS bytes [dst + 16 i, +16) of
+// the wave-uniform destination `dst`.  Issued through inline asm so that the
+// compiler's wait-count pass does not treat every later LDS read as a possible
+// alias (it would wait for the prefetch of the next tile); the loops wait for
+// these loads explicitly (s_waitcnt vmcnt + barrier).
+__device__ __forceinline__ void dma16(const void* base, uint32_t voff, const unsigned char MLA_LDS* dst) {
+  const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)dst);
+  // the base is wave-uniform; make that explicit so it is held in scalar registers.
+  // readfirstlane returns a signed int: zero-extend each half through uint32_t.
+  const uint64_t b = (uint64_t)(uintptr_t)base;
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint64_t bs = ((uint64_t)hi << 32) | (uint64_t)lo;
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :: "v"(voff), "s"(bs), "s"(m0) : "memory", "m0");
+}
+
+// all but the latest N of this wave's direct loads have landed and its LDS reads
+// are done; then all waves meet
+template <int N>
+__device__ __forceinline__ void dma_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
+}
+
 __device__ __forceinline__ float bf16_lo(uint32_t v) { return __uint_as_float(v << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t v) { return __uint_as_float(v & 0xffff0000u); }
 

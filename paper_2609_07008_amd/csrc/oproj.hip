@@ -47,7 +47,6 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles) {
   __shared__ __attribute__((aligned(16))) uint16_t As[OP_BM * OP_ALD];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[OP_BK * OP_BLD];
   __shared__ int row_flag[OP_BM];
-  __shared__ int row_out[OP_BM];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hpg = a.n_heads / a.n_groups;
@@ -95,10 +94,7 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles) {
       }
       run[tid] = lo;
     }
-    for (int i = tid; i < OP_BM; i += NT) {
-      row_flag[i] = 0;
-      row_out[i] = m0 + i < M ? m0 + i : -1;
-    }
+    for (int i = tid; i < OP_BM; i += NT) row_flag[i] = 0;
     __syncthreads();
     for (int k = run[0] + tid; k < run[1]; k += NT) {
       const int64_t r = (int64_t)a.prot_rows[k] - m0;
@@ -229,9 +225,8 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles) {
         for (int p = 0; p < 4; ++p) {
           const int n = n0 + wn * TN + ni * 32 + pc4;
           const int r = wm * TM + mi * 32 + p * 8 + prow;
-          const int64_t orow = m0 + r < M && n < cw ? (int64_t)row_out[r] : -1;
-          const bool use = has_zoff && orow >= 0 && !row_flag[r];
-          const u32x2 zz = *(const u32x2*)(zoff + (use ? orow * a.d_model + (int64_t)pg * cw + n : 0));
+          const bool use = has_zoff && m0 + r < M && n < cw && !row_flag[r];
+          const u32x2 zz = *(const u32x2*)(zoff + (use ? (int64_t)(m0 + r) * a.d_model + (int64_t)pg * cw + n : 0));
           addv[ni][p] = use ? zz : u32x2{0u, 0u};
         }
 #pragma unroll
@@ -255,9 +250,7 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles) {
         f32x4 v = *(const f32x4 MLA_LDS*)(stage + rr * SLD + pc4);
         const int r = wm * TM + mi * 32 + rr;       // tile row
         if (m0 + r >= M || n >= cw) continue;
-        const int64_t orow = row_out[r];
-        if (orow < 0) continue;
-        const int64_t off = orow * a.d_model + (int64_t)pg * cw + n;
+        const int64_t off = (int64_t)(m0 + r) * a.d_model + (int64_t)pg * cw + n;
         v += addf[ni][p];
         if (a.z_bf16)
           *(u32x2*)((uint16_t*)a.z + off) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
@@ -281,22 +274,6 @@ void oproj_kernel(OprojArgs a, int m_tiles, int n_tiles) {
 // 296 (64 heads); 4014 rows of 128 heads 300 -> 254.
 constexpr int OL_WAVES = 8, OL_GRID = 256;
 constexpr int OL_LDS = 147456;                 // the largest variant's slices
-
-__device__ __forceinline__ void ol_dma16(const unsigned char* base, uint32_t voff, const unsigned char MLA_LDS* dst) {
-  const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)dst);
-  const uint64_t b = (uint64_t)(uintptr_t)base;
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-  const uint64_t bs = ((uint64_t)hi << 32) | (uint64_t)lo;
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(voff), "s"(bs), "s"(m0) : "memory", "m0");
-}
-// all but the latest N of this wave's direct loads have landed and its LDS reads
-// are done; then all waves meet
-template <int N>
-__device__ __forceinline__ void ol_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
-}
 
 // weight row of K index k of projection group pg's Local heads
 __device__ __forceinline__ int local_w_row(const OprojArgs& a, int pg, int k) {
@@ -360,7 +337,7 @@ __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned 
     }
     auto load_one = [&](int j, int kt, int64_t wk, int st) {
       const int q = std::min(wave + OL_WAVES * j, NLOADS - 1);
-      ol_dma16(src[j] + (q < NA ? (int64_t)kt * 128 : wk), voff[j], (const unsigned char MLA_LDS*)(lds + st + 1024 * q));
+      dma16(src[j] + (q < NA ? (int64_t)kt * 128 : wk), voff[j], (const unsigned char MLA_LDS*)(lds + st + 1024 * q));
     };
     // byte offset of the next slice's first weight row: a slice never straddles two
     // heads, whose rows are consecutive
@@ -428,7 +405,7 @@ __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned 
 #pragma unroll
         for (int j = 0; j < LPW; ++j) load_one(j, p, wk, p * STAGE);
       }
-    if (nk >= NST) ol_barrier<(NST - 1) * LPW>(); else ol_barrier<0>();
+    if (nk >= NST) dma_barrier<(NST - 1) * LPW>(); else dma_barrier<0>();
     Frags f0, f1;
 #pragma unroll
     for (int j = 0; j < NI; ++j) f0.b[j] = frag_b(0, 0, j);
@@ -438,14 +415,14 @@ __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned 
     for (; kt + NST < nk; ++kt) {
       const int64_t wk = next_w();
       half(f0, f1, st, 1, std::false_type{}, 0, 0, 0);
-      ol_barrier<(NST - 2) * LPW>();
+      dma_barrier<(NST - 2) * LPW>();
       const int nst = st == (NST - 1) * STAGE ? 0 : st + STAGE;
       half(f1, f0, nst, 0, std::true_type{}, kt + NST, wk, st);
       st = nst;
     }
     for (; kt < nk; ++kt) {
       half(f0, f1, st, 1, std::false_type{}, 0, 0, 0);
-      ol_barrier<0>();
+      dma_barrier<0>();
       const int nst = st == (NST - 1) * STAGE ? 0 : st + STAGE;
       half(f1, f0, nst, 0, std::false_type{}, 0, 0, 0);   // after the last slice: stale, not used
       st = nst;
@@ -465,7 +442,7 @@ __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned 
         const int r = a.prot_rows[std::min(m, M - 1)];
         orow[i][p] = m < M && n < cw && r >= 0 && r < a.n_rows ? r : -1;   // outside z: skipped
       }
-    ol_barrier<0>();
+    dma_barrier<0>();
     unsigned char MLA_LDS* sw = (unsigned char MLA_LDS*)lds + wave * 8192;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
@@ -496,7 +473,7 @@ __device__ __forceinline__ void local_tiles(const OprojArgs& a, int M, unsigned 
           *(f32x4*)(a.z + off) = v;
       }
     }
-    ol_barrier<0>();   // the next tile's slices may come in
+    dma_barrier<0>();   // the next tile's slices may come in
   }
 }
 
@@ -568,11 +545,7 @@ __global__ __launch_bounds__(256) void local_wt_kernel(OprojArgs a, uint16_t* wt
     const int n = nt * 64 + tx;
     uint16_t v = 0;
     if (k < KL && n < cw) {
-      const int kb = (int)(k / DC), d = (int)(k - (int64_t)kb * DC);
-      const int gl = kb / (hpg - 1), j = kb - gl * (hpg - 1);
-      const int gh = a.glob_head[pg * gpp + gl];
-      const int hl = gl * hpg + (j < gh ? j : j + 1);
-      v = W[((int64_t)hl * DC + d) * cw + n];
+      v = W[(int64_t)local_w_row(a, pg, (int)k) * cw + n];
     }
     tile[r][tx] = v;
   }

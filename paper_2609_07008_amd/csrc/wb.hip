@@ -37,23 +37,6 @@ constexpr int WB_ROWB = WB_BK * 2;                    // bytes of one row of a s
 constexpr int64_t kWbFewRows = 32, kWbFewBlocks = 512;   // largest requests of the few-row kernel
 constexpr int WB_GM = 8;                              // row panels per column panel in the tile walk
 
-__device__ __forceinline__ void wb_dma16(const void* base, uint32_t voff, const unsigned char MLA_LDS* dst) {
-  const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)dst);
-  const uint64_t b = (uint64_t)(uintptr_t)base;
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-  const uint64_t bs = ((uint64_t)hi << 32) | (uint64_t)lo;
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(voff), "s"(bs), "s"(m0) : "memory", "m0");
-}
-
-// all but the latest N of this wave's direct loads have landed and its LDS reads
-// are done; then all waves meet
-template <int N>
-__device__ __forceinline__ void wb_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
-}
-
 __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
 // MI: 16-row blocks per wave (tile of 32 MI rows x BN channels); NST: K slices in LDS
@@ -101,7 +84,7 @@ __global__ __launch_bounds__(WB_WAVES * 64, 2) void wb_gemm_kernel(WbArgs a, int
     dst[j] = 1024 * q;
   }
   auto load_one = [&](int j, int kt, int st) {
-    wb_dma16(src[j] + (int64_t)kt * WB_ROWB, voff[j], (const unsigned char MLA_LDS*)(lds + st + dst[j]));
+    dma16(src[j] + (int64_t)kt * WB_ROWB, voff[j], (const unsigned char MLA_LDS*)(lds + st + dst[j]));
   };
 
   f32x4 acc[MI][NI];
@@ -159,7 +142,7 @@ __global__ __launch_bounds__(WB_WAVES * 64, 2) void wb_gemm_kernel(WbArgs a, int
     if (p < nk)
 #pragma unroll
       for (int j = 0; j < LPW; ++j) load_one(j, p, p * STAGE);
-  if (nk >= NST) wb_barrier<(NST - 1) * LPW>(); else wb_barrier<0>();
+  if (nk >= NST) dma_barrier<(NST - 1) * LPW>(); else dma_barrier<0>();
   Frags f0, f1;
 #pragma unroll
   for (int j = 0; j < NI; ++j) f0.b[j] = frag(fb, 0, 0, j);
@@ -168,14 +151,14 @@ __global__ __launch_bounds__(WB_WAVES * 64, 2) void wb_gemm_kernel(WbArgs a, int
   int st = 0, kt = 0;
   for (; kt + NST < nk; ++kt) {
     half(f0, f1, st, 1, std::false_type{}, 0, 0);
-    wb_barrier<(NST - 2) * LPW>();
+    dma_barrier<(NST - 2) * LPW>();
     const int nst = st == (NST - 1) * STAGE ? 0 : st + STAGE;
     half(f1, f0, nst, 0, std::true_type{}, kt + NST, st);
     st = nst;
   }
   for (; kt < nk; ++kt) {
     half(f0, f1, st, 1, std::false_type{}, 0, 0);
-    wb_barrier<0>();
+    dma_barrier<0>();
     const int nst = st == (NST - 1) * STAGE ? 0 : st + STAGE;
     half(f1, f0, nst, 0, std::false_type{}, 0, 0);   // after the last slice: reads of a stale buffer, not used
     st = nst;
@@ -185,7 +168,7 @@ __global__ __launch_bounds__(WB_WAVES * 64, 2) void wb_gemm_kernel(WbArgs a, int
   // accumulator layout (row lc, channels lg*4 .. +3 of each block; 16-byte chunk c
   // of row r at c ^ (r & SW)), read back row-contiguous, so that each store writes
   // whole 128-byte lines.
-  wb_barrier<0>();
+  dma_barrier<0>();
   constexpr int ES = OUT_BF16 ? 2 : 4, ROW = BN / 4 * ES;   // element and row bytes
   constexpr int CH = ROW / 16, RPI = 64 / CH;           // 16-byte chunks a row, rows a store
   constexpr int SW = CH < 8 ? CH - 1 : 7;
@@ -262,7 +245,7 @@ __global__ __launch_bounds__(WB_WAVES * 64) void wb_rows_kernel(WbArgs a, int n_
     for (int j = 0; j < LPW; ++j) {
       const int r = wave * LPW + j;
       const uint32_t at = std::min((uint32_t)(s * ROWB + (lane ^ (r & 15)) * 16), (uint32_t)(a.d_in * 2 - 16));
-      wb_dma16(src[j], at, (const unsigned char MLA_LDS*)(lds + st + r * ROWB));
+      dma16(src[j], at, (const unsigned char MLA_LDS*)(lds + st + r * ROWB));
     }
   };
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -273,7 +256,7 @@ __global__ __launch_bounds__(WB_WAVES * 64) void wb_rows_kernel(WbArgs a, int n_
   int st = 0;
   for (int s = 0; s < ns; ++s) {
     // stage s has landed, and every wave has read stage s - 1, whose buffer is next
-    wb_barrier<(NST - 2) * LPW>();
+    dma_barrier<(NST - 2) * LPW>();
     load(s + NST - 1, st == 0 ? (NST - 1) * STAGE : st - STAGE);
     if (wave < MB) {
       const unsigned char MLA_LDS* pw = L + st + lc * ROWB;
@@ -298,7 +281,7 @@ __global__ __launch_bounds__(WB_WAVES * 64) void wb_rows_kernel(WbArgs a, int n_
     }
     st = st == (NST - 1) * STAGE ? 0 : st + STAGE;
   }
-  wb_barrier<0>();   // the loads past the end have landed
+  dma_barrier<0>();   // the loads past the end have landed
   if (wave >= MB) return;
   const int64_t m = wave * 16 + lc;
   if (m >= a.n_rows) return;
