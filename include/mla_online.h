@@ -337,7 +337,7 @@ mla_status mla_online_attend_planned_noalloc(const mla_geom* geom, const mla_pla
  *  prot_rows, n_prot  as for mla_online_attend_planned (entries outside [0, N)
  *             are skipped by the Local pass, as in mla_sliced_oproj_add)
  *  z_dtype    MLA_F32 or MLA_BF16 (the latter is what mla_shared_wb takes; a
- *             protected row then carries the rounding of its Local sum and of z)
+ *             protected row then carries the rounding of its Global sum and of z)
  * Errors: NULL, SHAPE, UNSUPPORTED, HIP. */
 mla_status mla_sliced_oproj_add_planned(const mla_geom* geom, const mla_plan_info* info, const void* o_glob,
                                         const void* o_loc, const int32_t* glob_head, const int32_t* prot_rows,

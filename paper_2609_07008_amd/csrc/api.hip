@@ -1067,7 +1067,7 @@ mla_status mla_offline_produce(const mla_geom* geom, const mla_segment* segs, in
     return fail(MLA_ERR_UNSUPPORTED, "%lld rows x d_model %d is more o-proj tiles than one launch takes",
                 (long long)N, geom->d_model);
   {
-    // the Local projection's direct loads address a wave's 64 rows with 32-bit offsets
+    // the Local projection's direct loads address 8 rows with 32-bit offsets; held to 64 rows
     const int64_t ldz = (int64_t)geom->n_groups * (hpg - 1) * head_dv(geom);
     if (64 * ldz * 2 >= ((int64_t)1 << 32))
       return fail(MLA_ERR_UNSUPPORTED, "Local head outputs of %lld elements a row", (long long)ldz);

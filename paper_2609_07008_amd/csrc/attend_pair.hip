@@ -35,10 +35,11 @@
 // the first tile: 27K clk from a workgroup's start to its first tile against 16K).
 // Head outputs leave through LDS as whole rows.
 //
-// Measured against the one-wave kernel (same box, whole calls): the 264,192-row
-// step 608 -> 543 ms, the 33,792-row one 12.8 -> 11.4, the 67,584-row one with 128
-// heads 106 -> 95.4, the 33K-row producer 5.09 -> 4.74, the 2.1K-row step 0.245 ->
-// 0.227; 3060 clk per 32 keys and workgroup at 1.95 GHz against 3630 at 2.1.  Without
+// Measured against the one-wave kernel (same box, whole calls, the other kernels'
+// changes included): the 264,192-row step 594 -> 531 ms, the 33,792-row one 12.2 ->
+// 10.9, with partials 11.4 -> 10.5, the 67,584-row one with 128 heads 102.5 -> 91.3, the
+// 33K-row producer 5.03 -> 4.63; this kernel alone took the 2.1K-row step from 245 to
+// 227 us.  3060 clk per 32 keys and workgroup at 1.95 GHz against 3630 at 2.1.  Without
 // the value waves' MFMAs a step takes 2350 clk, without the score waves' 2640.
 // Reading V or K two, three or four fragments ahead, wave priorities and the tile
 // loads' place in the step change the clock and the cycles together and leave the
@@ -48,9 +49,10 @@
 // first 64 keys as in the one-wave kernel: tiles 0 and 1 are loaded together and the
 // score waves run K Q^T over them once for the max alone.  From the first 16 keys,
 // inside the first step, it cost nothing, but rounded the weight of every larger key
-// after them (errors against 64 bits up to 5 % larger, and outputs 2^-9 of their value
-// off the one-wave kernel's; now 1e-4 and less).  The pass takes an item about 3K clk:
-// the 33K-row producer 4.59 -> 4.72 ms, the steps 1 % at most.
+// after them: errors against 64 bits grew (2.1K-row step, lse 1.83e-5 -> 1.89e-5; now
+// 1.83e-5), and outputs were 1e-3 to 2.7e-3 off the one-wave kernel's (now 2e-4 and
+// less, the order of the sums).  The pass takes an item about 3K clk, its MFMAs: the
+// 33K-row producer 4.51 -> 4.61 ms, steps up to 1 %, 1.6 % where documents are short.
 //
 // Restart policy: restart.h.  A wave that sees a tile's weights sum to 2^64 or more
 // records the next step's index in restart_at (LDS atomic min); at the end of step

@@ -27,7 +27,7 @@
 //
 // What bounds it is vector issue: 64-bit rounds over all of a lane's experts took 278
 // wave instructions a row, these 115, 134 with repeated weights.  264,192 rows x 256
-// experts 127 -> 73 us (4.0 TB/s; bf16 logits 127 -> 84, all weights equal 127 -> 102),
+// experts 127 -> 73 us (3.9 TB/s; bf16 logits 127 -> 84, all weights equal 127 -> 102),
 // x 128 83 -> 51, x 64 68 -> 45, x 16 52 -> 33.  Any two neighbours with like upper bits,
 // equal weights too, sent to the exact ranking took bf16 logits 160 us.  Four waves a
 // SIMD (at most 128 registers): with fewer registers the exact ranking spills (110 us),

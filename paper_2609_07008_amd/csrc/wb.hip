@@ -4,9 +4,9 @@
 // K-contiguous, so this is C = A B^T with A = z, B = W_b, on bf16 MFMA with fp32
 // accumulation; y is written in fp32 or bf16.
 //
-// Tiles of 32 MI rows x BN channels (256; 128 at up to about 1000 rows) per workgroup
-// of 8 waves (2 x 4, each 16 MI x BN / 4); the operands come in by direct global->LDS loads, 64 of K at a time, NST
-// slices in LDS.  On a full chip power is what bounds it: 16x16x32 MFMAs take less
+// Tiles of 32 MI rows x BN channels (256; 128 while a round over the chip is not full,
+// and for narrow outputs) per workgroup of 8 waves (2 x 4, each 16 MI x BN / 4); the
+// operands come in by direct global->LDS loads, 64 of K at a time, NST slices in LDS.  On a full chip power is what bounds it: 16x16x32 MFMAs take less
 // per flop than 32x32x16 (see attend_pair.hip), so a wave's 16-row fragments feed
 // MI x 4 of them, neighbours sharing an operand.  What stalls it otherwise is the
 // barrier of a slice: it sits between a step's two halves, so that a half's MFMAs,

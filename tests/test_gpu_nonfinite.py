@@ -6,7 +6,7 @@ must come out non-finite (no reference max can repair a NaN or infinite score;
 IEEE arithmetic carries it into O, lse and z).  Every row that cannot see j is
 unaffected, bit for bit, with one documented exception: a row of j's own
 document that shares j's work item (a run of at most 128 head-rows) and its
-64-key tile multiplies j's latent by a zero weight on the matrix cores, and
+key tile (32 keys, 64 in the one-wave kernel) multiplies j's latent by a zero weight on the matrix cores, and
 0 * inf and 0 * NaN are NaN; such a row's elements are either bit-identical to
 the clean run or non-finite.  An infinite score makes the restart vote fire on
 every pass, so it also exercises the bounded number of passes of a work item;
