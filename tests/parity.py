@@ -88,7 +88,7 @@ def compare_rows(wl, st, rows, z_off, kv=None, keys=None, lse_abs_tol=ABS_TOL, z
                           for r, p in zip(rows, prot)])
     if z_bf16:
         # z stored in bf16: each element carries up to two roundings of 2^-9 |z|
-        # (a protected row's Local sum, then z), which z - z_off inherits
+        # (a protected row's Global sum, then z), which z - z_off inherits
         allow = z_abs_tol + 2.0 ** -8 * np.abs(ref.z)
         assert np.all(np.abs(z - zoff_rows - ref.z_online) <= allow), "z_online (bf16 z)"
         check("z", z, ref.z, abs_tol=z_abs_tol, bf16_out=True)
